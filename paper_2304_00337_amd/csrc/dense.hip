@@ -1,7 +1,7 @@
 // Dense kernels of the iteration (Section 4 and 5) for gfx950:
 //  * coarsest-level direct solve: the coarse operator is assembled by applying the stencil
-//    to unit vectors, inverted in place by Gauss-Jordan (Hermitian positive definite, no
-//    pivoting) in one workgroup, and applied as a dense matrix-vector product;
+//    to unit vectors, inverted in place by block Gauss-Jordan steps (Hermitian positive
+//    definite, no pivoting), and applied as a dense matrix-vector product;
 //  * tall-skinny Gram products X^* W of planar FP64 blocks (LDS-staged, register-tiled);
 //  * block recombination S Y.
 #include "internal.h"
@@ -65,55 +65,212 @@ void add_constant_rank_one(double* mat, int64_t n, double gamma, const Launch& L
   k_add_rank_one<<<dim3((unsigned)((n * n + 255) / 256), (unsigned)L.nact), 256, 0, L.st>>>(mat, n, gamma, L.slots);
 }
 
-// In-place Gauss-Jordan inversion of a Hermitian positive definite matrix (no pivoting),
-// one workgroup per slot.
-__global__ __launch_bounds__(1024) void k_invert(c2* __restrict__ A, int n, const int* __restrict__ slots) {
-  extern __shared__ c2 colk[];
-  __shared__ c2 piv;
-  A += (int64_t)(slots ? slots[blockIdx.x] : (int)blockIdx.x) * n * n;
-  for (int k = 0; k < n; ++k) {
-    if (threadIdx.x == 0) {
-      const c2 a = A[(int64_t)k * n + k];
-      const double d = a.r * a.r + a.i * a.i;
-      piv = {a.r / d, -a.i / d};
-    }
-    for (int i = threadIdx.x; i < n; i += blockDim.x) colk[i] = A[(int64_t)i * n + k];
-    __syncthreads();
-    const c2 p = piv;
-    for (int j = threadIdx.x; j < n; j += blockDim.x) {
-      if (j != k) A[(int64_t)k * n + j] = cm(A[(int64_t)k * n + j], p);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) A[(int64_t)k * n + k] = p;
-    for (int64_t e = threadIdx.x; e < (int64_t)n * n; e += blockDim.x) {
-      const int i = (int)(e / n), j = (int)(e % n);
-      if (i == k) continue;
-      const c2 f = colk[i];
-      if (j == k) {
-        const c2 v = cm(f, p);
-        A[e] = {-v.r, -v.i};
-      } else {
-        const c2 v = cm(f, A[(int64_t)k * n + j]);
-        A[e] = {A[e].r - v.r, A[e].i - v.i};
-      }
-    }
-    __syncthreads();
-  }
-}
-void invert_hpd(double* mat, int64_t n, const Launch& L) {
-  if (L.nact <= 0) return;
-  k_invert<<<L.nact, 1024, (size_t)n * sizeof(c2), L.st>>>(reinterpret_cast<c2*>(mat), (int)n, L.slots);
+// In-place inversion of Hermitian positive definite matrices by block Gauss-Jordan steps (no
+// pivoting), one launch per block column of IB unknowns, a workgroup per IB x IB tile, all slots
+// and both coarse matrices of a slot (edge and nodal) in the same launches.
+//
+// Bound by latency: n dependent pivots.  One workgroup per matrix sweeping scalar pivots streams
+// the whole matrix through one compute unit at each of them: 618 + 176 us for the 128 edges and
+// 64 nodes of an 8 x 8 level, 4.9 + 1.2 ms for the 270 and 135 of a 15 x 9 one.  Here a step
+// takes IB pivots at once and its tiles spread over the device, so the chain is n / IB launches
+// of 19 us: 81 us and 176 us for both matrices.  Every workgroup inverts the pivot block itself
+// (32 short steps in registers, one barrier each): less than another dependent launch costs.
+//
+// Step k replaces, with P the inverse of the pivot block, A_kk by P, A_kj by P A_kj, A_ik by
+// -A_ik P and A_ij by A_ij - A_ik P A_kj.  The other tiles of the step still read block row and
+// column k, so their new values go to panels (by step parity) and are read from there by step
+// k + 1, which writes them back; k_invert_finish writes the last step's panels back and the
+// single-precision copy.
+constexpr int IB = 32;
+
+struct InvMat {
+  c2* a;          // n x n per slot
+  float* a32;     // single-precision copy (2 n n values per slot)
+  c2* panel;      // 4 IB n per slot: row panels (2 x IB x n), then column panels (2 x n x IB)
+  int n;
+};
+
+// Tile (I, J) before step k: in the panels of step k - 1 or in the matrix (the same choice for
+// the whole workgroup, so that all of its loads can be issued together).
+struct InvTile {
+  const c2* p;
+  int64_t stride;
+};
+__device__ __forceinline__ InvTile inv_tile(const InvMat& M, int64_t slot, int k, int I, int J) {
+  const int64_t n = M.n, par = (k - 1) & 1;
+  const c2* pan = M.panel + slot * 4 * IB * n;
+  if (k > 0 && I == k - 1) return {pan + par * IB * n + J * IB, n};
+  if (k > 0 && J == k - 1) return {pan + 2 * IB * n + (par * n + (int64_t)I * IB) * IB, IB};
+  return {M.a + slot * n * n + (int64_t)I * IB * n + (int64_t)J * IB, n};
 }
 
-__global__ void k_mat_to_float(const double* __restrict__ in, float* __restrict__ out, int64_t count,
-                               const int* __restrict__ slots) {
-  const int64_t s = slots ? slots[blockIdx.y] : blockIdx.y;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) out[s * count + i] = (float)in[s * count + i];
+__global__ __launch_bounds__(256) void k_invert_step(InvMat me, InvMat mn, int k, const int* __restrict__ slots) {
+  const InvMat M = (blockIdx.z & 1) ? mn : me;
+  const int64_t slot = slots ? slots[blockIdx.z >> 1] : (int)(blockIdx.z >> 1);
+  const int nb = (M.n + IB - 1) / IB;
+  const int I = (int)blockIdx.y, J = (int)blockIdx.x;
+  if (k >= nb || I >= nb || J >= nb) return;
+  __shared__ c2 P[IB][IB + 1], X[IB][IB + 1], Y[IB][IB + 1];
+  __shared__ c2 rowb[2][IB], colb[2][IB];
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  // pivot block, own tile, and the tile's blocks of block column and row k: every load issued
+  // before the first use (entries past the matrix read entry 0 of their tile and are replaced by
+  // the identity in the pivot block, by zero elsewhere)
+  double er[2][2], ei[2][2];   // (apart, so that the selects below keep them in registers)
+  c2 own[2][2], xv[2][2], yv[2][2];
+  const InvTile tp = inv_tile(M, slot, k, k, k), to = inv_tile(M, slot, k, I, J), tc = inv_tile(M, slot, k, I, k),
+                tr = inv_tile(M, slot, k, k, J);
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int i = ty + 16 * a, j = tx + 16 * b;
+      const bool pi = IB * k + i < M.n, pj = IB * k + j < M.n, oi = IB * I + i < M.n, oj = IB * J + j < M.n;
+      const c2 v = tp.p[pi && pj ? i * tp.stride + j : 0];
+      own[a][b] = to.p[oi && oj ? i * to.stride + j : 0];
+      xv[a][b] = tc.p[oi && pj ? i * tc.stride + j : 0];
+      yv[a][b] = tr.p[pi && oj ? i * tr.stride + j : 0];
+      er[a][b] = v.r;
+      ei[a][b] = v.i;
+    }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int i = ty + 16 * a, j = tx + 16 * b;
+      const bool pi = IB * k + i < M.n, pj = IB * k + j < M.n, oi = IB * I + i < M.n, oj = IB * J + j < M.n;
+      er[a][b] = pi && pj ? er[a][b] : (i == j ? 1.0 : 0.0);
+      ei[a][b] = pi && pj ? ei[a][b] : 0.0;
+      X[i][j] = c2{oi && pj ? xv[a][b].r : 0.0, oi && pj ? xv[a][b].i : 0.0};
+      Y[i][j] = c2{pi && oj ? yv[a][b].r : 0.0, pi && oj ? yv[a][b].i : 0.0};
+    }
+#pragma unroll
+  for (int hi = 0; hi < 2; ++hi)   // the pivot's register row and column are compile-time indices
+#pragma unroll 1
+  for (int lo = 0; lo < 16; ++lo) {
+    const int s = 16 * hi + lo, par = s & 1;
+    if (ty == lo) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b) rowb[par][tx + 16 * b] = c2{er[hi][b], ei[hi][b]};
+    }
+    if (tx == lo) {
+#pragma unroll
+      for (int a = 0; a < 2; ++a) colb[par][ty + 16 * a] = c2{er[a][hi], ei[a][hi]};
+    }
+    __syncthreads();
+    const c2 pv = rowb[par][s];
+    const c2 r0 = rowb[par][tx], r1 = rowb[par][tx + 16], f0 = colb[par][ty], f1 = colb[par][ty + 16];
+    const double d = 1.0 / (pv.r * pv.r + pv.i * pv.i);
+    const c2 p = {pv.r * d, -pv.i * d};
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const bool pc = tx + 16 * b == s;   // the pivot column
+      const c2 q = cm(b ? r1 : r0, p);
+      const double qr = pc ? p.r : q.r, qi = pc ? p.i : q.i;
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        const bool prow = ty + 16 * a == s;   // the pivot row
+        const c2 v = cm(a ? f1 : f0, c2{qr, qi});
+        er[a][b] = prow ? qr : (pc ? 0.0 : er[a][b]) - v.r;
+        ei[a][b] = prow ? qi : (pc ? 0.0 : ei[a][b]) - v.i;
+      }
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) P[ty + 16 * a][tx + 16 * b] = c2{er[a][b], ei[a][b]};
+  __syncthreads();
+  // C = A B over the 32-wide blocks, 2 x 2 entries per thread
+  auto mul = [&](const c2(*A)[IB + 1], const c2(*B)[IB + 1], c2(&c)[2][2]) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) c[a][b] = c2{0.0, 0.0};
+#pragma unroll 4
+    for (int l = 0; l < IB; ++l) {
+      const c2 a0 = A[ty][l], a1 = A[ty + 16][l], b0 = B[l][tx], b1 = B[l][tx + 16];
+      const c2 av[2] = {a0, a1}, bv[2] = {b0, b1};
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          c[a][b].r = fma(-av[a].i, bv[b].i, fma(av[a].r, bv[b].r, c[a][b].r));
+          c[a][b].i = fma(av[a].i, bv[b].r, fma(av[a].r, bv[b].i, c[a][b].i));
+        }
+    }
+  };
+  c2 out[2][2];
+  if (I == k && J == k) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) out[a][b] = c2{er[a][b], ei[a][b]};
+  } else if (I == k) {
+    mul(P, Y, out);
+  } else if (J == k) {
+    mul(X, P, out);
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) out[a][b] = c2{-out[a][b].r, -out[a][b].i};
+  } else {
+    c2 t[2][2];
+    mul(P, Y, t);
+    __syncthreads();   // (uniform over the workgroup) Y is replaced by P Y
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) Y[ty + 16 * a][tx + 16 * b] = t[a][b];
+    __syncthreads();
+    mul(X, Y, t);
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) out[a][b] = c2{own[a][b].r - t[a][b].r, own[a][b].i - t[a][b].i};
+  }
+  const int64_t n = M.n, par = k & 1;
+  c2* pan = M.panel + slot * 4 * IB * n;
+  c2* A = M.a + slot * n * n;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int i = IB * I + ty + 16 * a, j = IB * J + tx + 16 * b;
+      if (i >= n || j >= n) continue;
+      if (I == k) pan[(par * IB + i % IB) * n + j] = out[a][b];
+      else if (J == k) pan[2 * IB * n + (par * n + i) * IB + j % IB] = out[a][b];
+      else A[(int64_t)i * n + j] = out[a][b];
+    }
 }
-void matrix_to_float(const double* mat, float* out, int64_t count, const Launch& L) {
+
+// The last step's panels back into the matrix, and its single-precision copy.
+__global__ __launch_bounds__(256) void k_invert_finish(InvMat me, InvMat mn, const int* __restrict__ slots) {
+  const InvMat M = (blockIdx.y & 1) ? mn : me;
+  const int64_t slot = slots ? slots[blockIdx.y >> 1] : (int)(blockIdx.y >> 1);
+  const int64_t n = M.n, e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= n * n) return;
+  const int i = (int)(e / n), j = (int)(e % n), nb = (M.n + IB - 1) / IB;
+  const InvTile t = inv_tile(M, slot, nb, i / IB, j / IB);
+  const c2 v = t.p[(int64_t)(i % IB) * t.stride + j % IB];
+  if (i / IB == nb - 1 || j / IB == nb - 1) M.a[slot * n * n + e] = v;
+  float* o = M.a32 + 2 * (slot * n * n + e);
+  o[0] = (float)v.r;
+  o[1] = (float)v.i;
+}
+
+size_t invert_panel_doubles(int64_t ne, int64_t nn) { return (size_t)8 * IB * (ne + nn); }
+
+void invert_coarse(double* ke, float* ke32, int64_t ne, double* kn, float* kn32, int64_t nn, int nslots, double* panel,
+                   const Launch& L) {
   if (L.nact <= 0) return;
-  k_mat_to_float<<<dim3((unsigned)((count + 255) / 256), (unsigned)L.nact), 256, 0, L.st>>>(mat, out, count, L.slots);
+  const InvMat me{reinterpret_cast<c2*>(ke), ke32, reinterpret_cast<c2*>(panel), (int)ne};
+  const InvMat mn{reinterpret_cast<c2*>(kn), kn32, reinterpret_cast<c2*>(panel) + (size_t)nslots * 4 * IB * ne, (int)nn};
+  const int64_t big = ne > nn ? ne : nn;
+  const unsigned nb = (unsigned)((big + IB - 1) / IB);
+  for (unsigned k = 0; k < nb; ++k)
+    k_invert_step<<<dim3(nb, nb, (unsigned)(2 * L.nact)), 256, 0, L.st>>>(me, mn, (int)k, L.slots);
+  k_invert_finish<<<dim3((unsigned)((big * big + 255) / 256), (unsigned)(2 * L.nact)), 256, 0, L.st>>>(me, mn, L.slots);
 }
 
 // x = Inv_s b for a Hermitian Inv_s (row-major interleaved); row i of Inv_s is read as the

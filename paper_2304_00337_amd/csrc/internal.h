@@ -253,9 +253,11 @@ void nodal_vcycle_fused(View<const T> b, View<T> x, const CoarseCycle& C, const 
 void identity_block(double* out, int64_t n, hipStream_t st);
 void planar_to_matrix(const double* cols, int64_t n, double* mat, const Launch& L);
 void add_constant_rank_one(double* mat, int64_t n, double gamma, const Launch& L);
-void invert_hpd(double* mat, int64_t n, const Launch& L);
-// out[s * count + i] = (float) mat[s * count + i] on the launch's slots
-void matrix_to_float(const double* mat, float* out, int64_t count, const Launch& L);
+// The slots' coarse edge (ne x ne) and nodal (nn x nn) matrices replaced by their inverses, with
+// single-precision copies; panel: invert_panel_doubles(ne, nn) doubles for each of nslots slots.
+void invert_coarse(double* ke, float* ke32, int64_t ne, double* kn, float* kn32, int64_t nn, int nslots, double* panel,
+                   const Launch& L);
+size_t invert_panel_doubles(int64_t ne, int64_t nn);
 // x = Inv_s b per column, Inv_s = inv + s * n * n (complex, Hermitian)
 template <typename T>
 void dense_apply(const void* inv, int64_t n, View<const T> b, View<T> x, const Launch& L);

@@ -707,11 +707,8 @@ void setup_coarse(bl_solver* s, const std::vector<int>& slots) {
   }
   Launch L = make_launch(s, slots, 0);
   if (!gs.empty()) add_constant_rank_one(s->pc_inv64, s->ncn, s->ns.c0, make_launch(s, gs, 0));
-  invert_hpd(s->kc_inv64, s->nce, L);
-  matrix_to_float(s->kc_inv64, s->kc_inv32, 2 * s->nce * s->nce, L);
-  invert_hpd(s->pc_inv64, s->ncn, L);
-  matrix_to_float(s->pc_inv64, s->pc_inv32, 2 * s->ncn * s->ncn, L);
-  s->launches += 10;
+  invert_coarse(s->kc_inv64, s->kc_inv32, s->nce, s->pc_inv64, s->pc_inv32, s->ncn, s->nslots, s->gram_partial, L);
+  s->launches += 5 + (int)((s->nce + 31) / 32);
 }
 
 // Per-slot phases and zero thresholds to the device through the pinned staging area (it is
@@ -1024,7 +1021,8 @@ size_t engine_footprint(const bl_grid* grid, const bl_opts* o, int nslots) {
   Geo gc = make_geo(lv.back().first, lv.back().second, grid->a, grid->b);
   per += (size_t)gc.ne * gc.ne * 16 * 2 + (size_t)gc.nm * gc.nm * 16 * 2;   // inverses (FP64 + FP32)
   per += (size_t)gc.ne * gc.ne * 16;                                         // probe results
-  per += (size_t)rr_partial_blocks(g0) * q * q * 32 + (size_t)10 * q * q * 16;
+  // Rayleigh-Ritz partials (or the panels of the coarse inversions), Ritz matrices and work
+  per += std::max((size_t)rr_partial_blocks(g0) * q * q * 32, invert_panel_doubles(gc.ne, gc.nm) * 8) + (size_t)10 * q * q * 16;
   per += (size_t)p * ((g0.ne + 255) / 256) * 16;
   per += (size_t)q * pw_blocks(g0) * 16 + (size_t)q * 48 + (size_t)(grid->n + grid->m) * 16 + sizeof(PlaneWave);
   fixed += (size_t)gc.ne * gc.ne * 16 + (size_t)gc.nm * gc.nm * 16;           // probes
@@ -1128,7 +1126,9 @@ int engine_create(const bl_grid* grid, const bl_opts* opts, int nslots, hipStrea
   s->readback_bytes = rb * 8;
   if ((rc = dalloc_t(s, &s->partial, (size_t)p * S * apply_blocks(g0) * 2))) return fail(rc);
   s->gram_cap = (int64_t)rr_partial_blocks(g0) * q * q * 4 * S;
-  if ((rc = dalloc_t(s, &s->gram_partial, s->gram_cap))) return fail(rc);
+  // (shared with the panels of the coarse inversions: both are free between their launches)
+  const size_t scratch = std::max<size_t>(s->gram_cap, invert_panel_doubles(s->nce, s->ncn) * S);
+  if ((rc = dalloc_t(s, &s->gram_partial, scratch))) return fail(rc);
   if ((rc = dalloc_t(s, &s->Gm, (size_t)q * q * 2 * S))) return fail(rc);
   if ((rc = dalloc_t(s, &s->Hm, (size_t)q * q * 2 * S))) return fail(rc);
   if ((rc = dalloc_t(s, &s->Yd, (size_t)q * q * 2 * S))) return fail(rc);
