@@ -15,13 +15,14 @@ ROOT = os.path.dirname(PKG)
 SOURCES = ["csrc/stencils.hip", "csrc/dense.hip", "csrc/ritz.hip", "csrc/solver.hip",
            "csrc/abi.hip", "csrc/sched.hip", "csrc/rr.hip", "csrc/tune.hip", "csrc/coarse.hip",
            "csrc/sweep.hip", "csrc/planewave.hip",
-           "csrc/noalloc.hip"]
+           "csrc/noalloc.hip", "csrc/ritz_reg.hip"]
 LIB = os.path.join(PKG, "libbloch.so")
 # per-source flags: the block combination and the Ritz step's products keep their MFMA
 # accumulators in ordinary VGPRs (the default heuristic moves them between register files on
 # every step of their loops)
 EXTRA_FLAGS = {"csrc/dense.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-               "csrc/ritz.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+               "csrc/ritz.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+               "csrc/ritz_reg.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def hipcc() -> str:

@@ -288,6 +288,10 @@ void ritz_small(const double* G, const double* H, int q, int nfix, int want, con
                 double drop_rel, double* work, size_t work_stride, double* Y, double* theta,
                 int* count, const Launch& L);
 size_t ritz_small_work_doubles(int q);
+// ritz_small for q <= 112 in registers; false (nothing launched) when q is larger or the device
+// does not grant the kernel's LDS.
+bool ritz_registers(const double* G, const double* H, int q, int nfix, int want, const double* zthr, double drop_rel,
+                    double* work, size_t work_stride, double* Y, double* theta, int* count, const Launch& L);
 
 // out_s (want columns) = S_s (q columns) * Y_s (q x want, at Y + s * q * want * 2).
 void block_combine(View<const double> S, int q, const double* Y, int want, int64_t len,
