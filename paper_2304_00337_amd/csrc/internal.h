@@ -271,7 +271,7 @@ int gram_blocks(int64_t len);
 
 // Rayleigh-Ritz products straight from the basis (no stored M S or A S): per slot
 // G_s = S_s^* M S_s and H_s = S_s^* A S_s (q x q, row-major interleaved complex, at
-// G/H + s * q * q * 2).  q <= 48 runs on the matrix cores; wider bases on the vector units
+// G/H + s * q * q * 2).  q <= 144 runs on the matrix cores; wider bases on the vector units
 // with 48- or 64-wide output tiles (`tile` 3 or 4).  Returns -1 (nothing launched) when
 // partial_cap (doubles) is below rr_partial_blocks(g) * q * q * 4 * nact.
 int rr_gram(View<const double> S, int q, const double* kappa, const Geo& g, const Phase* ph,

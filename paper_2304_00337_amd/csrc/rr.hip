@@ -12,7 +12,8 @@
 // per node range are reduced in a fixed order, so a slot's G and H do not depend on the
 // other slots of the launch.
 //
-// Bases of at most 144 columns take the matrix cores instead: FP64 MFMA 16x16x4 products, the
+// Bases of at most 96 columns run in one launch on the matrix cores (k_rr_one below).  From there
+// to 144 columns, whose accumulators no workgroup holds, the matrix cores take them in groups: FP64 MFMA 16x16x4 products, the
 // columns cut into groups of 48 (three 16-column tiles): one launch for the diagonal blocks
 // (each group against itself, the upper tile pairs), one for the cross blocks (two groups
 // staged side by side, all nine tile pairs, mirrored into the lower triangle).  One
@@ -29,6 +30,7 @@
 #include "stencil_common.h"
 
 #include <type_traits>
+#include <utility>
 
 // Contractions are explicit (fma in the accumulations, none elsewhere), so the 48- and
 // 64-wide tile variants round identically.
@@ -610,6 +612,381 @@ __global__ __launch_bounds__(RR_THREADS) void k_rr_mfma(View<const double> Sv, i
   }
 }
 
+// ---- bases of at most 96 columns: every tile pair in one launch -------------------------------
+//
+// The mass matrix factors like A: on each line of parallel edges it is the circulant with 2/3 on
+// and 1/6 beside the diagonal, M = B^* B with (B u)_j = a u_j + b u_{j+1} (Bloch-extended),
+// a^2 + b^2 = 2/3 and a b = 1/6.  So G = Z^* Z with Z = B S (two values per node and column) as
+// H = W^* W with the scaled cell curls (one value), both Hermitian products of one operand.
+//
+// What bounds it is the FP64 matrix core: 16 x 16 tile pairs x three values x the real products
+// of a complex one.  Three of those suffice: off the diagonal (P1 = Ar Br, P2 = Ai Bi,
+// P3 = (Ar - Ai)(Br + Bi); Re = P1 + P2, Im = P3 - P1 + P2), and on it (Ar Ar + Ai Ai and
+// P = Ar Ai, Im = P - P^T).  A workgroup of eight waves walks the rows of a slice of 16 nodes and
+// holds all tile pairs (q = 84: 21 of G, 21 of H) spread over its waves by cost, so the basis is
+// read once; each row's values are formed once, by threads that keep their column's last x-edge
+// in registers, and go to LDS in the operand layout, double-buffered with one barrier per row.
+// On each SIMD one wave stages the next row before it multiplies and the other after, so that
+// staging and products overlap.
+// Measured (1024 x 1024): 1.90 ms at q = 84 against 1.84 + 1.57 ms with the basis in two groups of
+// 48 (each read twice, mass products formed per operand, four real products); the matrix cores
+// are busy 1.31 ms of it, the barriers and what the staging does not overlap are the rest.
+constexpr int kOneTiles = 6;
+constexpr int OW = 8;        // waves of a workgroup
+
+// The tasks of the waves: task t < P is tile pair t of G (six products per four nodes), P + t
+// that of H (three).  With few tiles the four-node groups of a row are split over KS sets of TW
+// waves.  Longest tasks first, each to the least loaded wave.
+template <int NT>
+struct OneConf {
+  static constexpr int P = NT * (NT + 1) / 2;
+  static constexpr int KS = NT == 1 ? 4 : (NT <= 3 ? 2 : 1), TW = OW / KS;
+  static constexpr int NC = 16 * NT, CP = NC + 1;   // (odd: no bank conflicts when staging)
+  static constexpr int ITEMS = (NC + 31) / 32;      // columns per thread
+  static constexpr int NACC = NT == 6 ? 16 : NT == 5 ? 11 : NT >= 3 ? 8 : NT == 2 ? 5 : 2;   // per wave
+};
+struct OnePlan {
+  int cnt[OW], nacc[OW];
+  int task[OW][8], at[OW][8];   // tasks and their first accumulators
+  bool ok;
+};
+constexpr int one_ti(int nt, int k) {
+  int i = 0;
+  while (k >= nt - i) {
+    k -= nt - i;
+    ++i;
+  }
+  return i;
+}
+constexpr int one_tj(int nt, int k) {
+  int i = 0;
+  while (k >= nt - i) {
+    k -= nt - i;
+    ++i;
+  }
+  return i + k;
+}
+template <int NT>
+constexpr OnePlan one_plan() {
+  using C = OneConf<NT>;
+  OnePlan p{};
+  int load[OW] = {};
+  p.ok = true;
+  for (int pass = 0; pass < 4; ++pass) {   // G off / on, H on / off the diagonal
+    const int type = pass / 2, diag = pass == 1 || pass == 2;
+    for (int k = 0; k < C::P; ++k) {
+      if ((one_ti(NT, k) == one_tj(NT, k)) != (diag == 1)) continue;
+      int w = 0;
+      for (int v = 1; v < C::TW; ++v)
+        if (load[v] < load[w] || (load[v] == load[w] && p.nacc[v] < p.nacc[w])) w = v;
+      if (p.cnt[w] >= 8) {
+        p.ok = false;
+        return p;
+      }
+      p.at[w][p.cnt[w]] = p.nacc[w];
+      p.task[w][p.cnt[w]++] = type * C::P + k;
+      p.nacc[w] += diag ? 2 : 3;
+      load[w] += type ? 3 : 6;
+      if (p.nacc[w] > C::NACC) p.ok = false;
+    }
+  }
+  return p;
+}
+
+template <int NT>
+struct OneStage {
+  double2 v[3][SW][OneConf<NT>::CP];   // Z x, Z y, W
+};
+
+// Task I of wave TWI, everything about it a constant.
+template <int NT, int TWI, int I>
+struct OneTask {
+  static constexpr OnePlan pl = one_plan<NT>();
+  static_assert(pl.ok, "task plan");
+  static constexpr int t = pl.task[TWI][I], k = t % OneConf<NT>::P, A = one_ti(NT, k), B = one_tj(NT, k),
+                       o = pl.at[TWI][I];
+  static constexpr bool is_h = t >= OneConf<NT>::P, diag = A == B;
+
+  __device__ static __forceinline__ void store(int lane, int q, double* pg, const d4* acc) {
+    double2* out = reinterpret_cast<double2*>(pg + (is_h ? (int64_t)q * q * 2 : 0));
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = 16 * A + 4 * v + (lane >> 4), col = 16 * B + (lane & 15);
+      if (row >= q || col >= q) continue;
+      const double a = acc[o][v], b = acc[o + 1][v];
+      if constexpr (diag) out[(int64_t)row * q + col] = double2{a, b};
+      else out[(int64_t)row * q + col] = double2{a + b, (acc[o + 2][v] - a) + b};
+    }
+  }
+};
+
+// Step SI of wave TWI: one value of one of its tasks (a task of G has two, of H one).
+template <int NT, int TWI, int SI>
+struct OneStep {
+  static constexpr OnePlan pl = one_plan<NT>();
+  static constexpr int find(bool value) {
+    int s = 0;
+    for (int i = 0; i < pl.cnt[TWI]; ++i)
+      for (int e = pl.task[TWI][i] < OneConf<NT>::P ? 0 : 2; e < (pl.task[TWI][i] < OneConf<NT>::P ? 2 : 3); ++e)
+        if (s++ == SI) return value ? e : i;
+    return -1;
+  }
+  using Task = OneTask<NT, TWI, find(false)>;
+  static constexpr int x = (find(true) * SW) * OneConf<NT>::CP + 16 * Task::A, y = x + 16 * (Task::B - Task::A);
+};
+template <int NT, int TWI>
+constexpr int one_steps() {
+  constexpr OnePlan pl = one_plan<NT>();
+  int s = 0;
+  for (int i = 0; i < pl.cnt[TWI]; ++i) s += pl.task[TWI][i] < OneConf<NT>::P ? 2 : 1;
+  return s;
+}
+
+// Steps SI .. NS - 1 on the four nodes at `at`, whose first operands are x and y; each step's
+// operands are read while the step before it multiplies (the last reads step 0's of `next`).
+template <int NT, int TWI, int SI, int NS>
+__device__ __forceinline__ void one_chain(const double2* at, const double2* next, d4* acc, double2& x, double2& y) {
+  using T = typename OneStep<NT, TWI, SI>::Task;
+  constexpr int o = T::o;
+  using N = OneStep<NT, TWI, SI + 1 < NS ? SI + 1 : 0>;
+  const double2* from = SI + 1 < NS ? at : next;
+  const double2 nx = from[N::x], ny = from[N::y];
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (T::diag) {
+    acc[o] = BL_MFMA(x.x, x.x, acc[o]);
+    acc[o + 1] = BL_MFMA(x.x, x.y, acc[o + 1]);
+    acc[o] = BL_MFMA(x.y, x.y, acc[o]);
+  } else {
+    const double d = x.x - x.y, e = y.x + y.y;
+    acc[o] = BL_MFMA(x.x, y.x, acc[o]);
+    acc[o + 1] = BL_MFMA(x.y, y.y, acc[o + 1]);
+    acc[o + 2] = BL_MFMA(d, e, acc[o + 2]);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  x = nx;
+  y = ny;
+  if constexpr (SI + 1 < NS) one_chain<NT, TWI, SI + 1, NS>(at, next, acc, x, y);
+}
+
+// The products of wave TWI's tasks over the four-node groups ks, ks + KS, ... of a staged row.
+template <int NT, int TWI>
+__device__ __forceinline__ void one_products(const OneStage<NT>& st, int ks, int lane, d4* acc) {
+  using C = OneConf<NT>;
+  using F = OneStep<NT, TWI, 0>;
+  const double2* at = &st.v[0][4 * ks + (lane >> 4)][lane & 15];
+  double2 x = at[F::x], y = at[F::y];
+#pragma unroll 1
+  for (int gq = ks; gq < SW / 4; gq += C::KS) {
+    const double2* next = gq + C::KS < SW / 4 ? at + 4 * C::KS * C::CP : at;
+    one_chain<NT, TWI, 0, one_steps<NT, TWI>()>(at, next, acc, x, y);
+    at = next;
+  }
+}
+
+// Wave TWI's sums to the workgroup's partial (G then H, q x q complex each): entries of tile
+// pairs off the diagonal as (Re, Im), of pairs on it as (Re, P), Im = P - P^T being left to the
+// reduction.  With KS > 1 the sets of waves are added through LDS first, in set order.
+template <int NT, int TWI, int... I>
+__device__ __forceinline__ void one_store(double* red, int ks, int lane, int q, double* pg, d4* acc,
+                                          std::integer_sequence<int, I...>) {
+  using C = OneConf<NT>;
+  if constexpr (C::KS > 1) {
+    double* mine = red + (size_t)TWI * C::NACC * 4 * 64 + lane;
+    for (int src = 1; src < C::KS; ++src) {
+      if (ks == src)
+#pragma unroll
+        for (int c = 0; c < C::NACC; ++c)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) mine[(c * 4 + v) * 64] = acc[c][v];
+      __syncthreads();
+      if (ks == 0)
+#pragma unroll
+        for (int c = 0; c < C::NACC; ++c)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[c][v] += mine[(c * 4 + v) * 64];
+      __syncthreads();
+    }
+    if (ks != 0) return;
+  }
+  (OneTask<NT, TWI, I>::store(lane, q, pg, acc), ...);
+}
+
+// run(TWI, its task indices) for the wave tw of TW; HALF 0 / 1: called by the first / second half of
+// the waves only, 2: by all
+template <int NT, int HALF, typename F>
+__device__ __forceinline__ void one_wave(int tw, F&& run) {
+  constexpr OnePlan pl = one_plan<NT>();
+#define BL_WAVE(w)                                                                                        \
+  case w:                                                                                                 \
+    if constexpr (w < OneConf<NT>::TW && (OneConf<NT>::KS > 1 || HALF == 2 || w / (OW / 2) == HALF))      \
+      run(std::integral_constant<int, w>{}, std::make_integer_sequence<int, pl.cnt[w]>{});                \
+    break;
+  switch (tw) {
+    BL_WAVE(0)
+    BL_WAVE(1)
+    BL_WAVE(2)
+    BL_WAVE(3)
+    BL_WAVE(4)
+    BL_WAVE(5)
+    BL_WAVE(6)
+    BL_WAVE(7)
+  }
+#undef BL_WAVE
+}
+
+template <int NT>
+__global__ __launch_bounds__(64 * OW) void k_rr_one(View<const double> Sv, int q, const double* __restrict__ kappa,
+                                                    Geo g, const Phase* __restrict__ phs, int slices, int band,
+                                                    double* __restrict__ partial, const int* __restrict__ slots) {
+  using C = OneConf<NT>;
+  constexpr int U = C::ITEMS;
+  extern __shared__ double lds[];
+  OneStage<NT>* st = reinterpret_cast<OneStage<NT>*>(lds);   // [2]
+  const int slot = slots ? slots[blockIdx.z] : (int)blockIdx.z;
+  const int64_t N = g.ne, nm = g.nm;
+  const int n = g.n, m = g.m;
+  const double* S = Sv.p + ((int64_t)slot * Sv.cps + Sv.off) * 2 * N;
+  const Ph<double> p = cast_phase<double>(phs[slot]);
+  const int c0 = (int)(blockIdx.x % slices) * SW;
+  const int r0 = (int)(blockIdx.x / slices) * band;
+  const int r1 = r0 + band < m ? r0 + band : m;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int tw = wv % C::TW, ks = wv / C::TW;
+  // this thread's node of the slice and its columns cc, cc + 32, ...; nodes past the grid and
+  // columns past the basis read a valid address and are staged as zero
+  const int jn = threadIdx.x & 15, cc = threadIdx.x >> 4;
+  const bool jok = c0 + jn < n;
+  const int j = jok ? c0 + jn : 0;
+  const int jr = j + 1 < n ? j + 1 : 0;      // right neighbour, times alpha across the period
+  const bool wrap = j + 1 >= n;
+  const double rt = 0.5773502691896257645;   // 1 / sqrt(3): a + b = 1, a - b = 1 / sqrt(3)
+  const double ma = 0.5 * (1.0 + rt), mb = 0.5 * (1.0 - rt);
+  const double sx = sqrt(g.mx), sy = sqrt(g.my);
+  const double* col0 = S + (int64_t)(cc < q ? cc : 0) * 2 * N + j;
+  auto column = [&](int u) { return col0 + (cc + 32 * u < q ? (int64_t)u * 64 * N : 0); };
+  double xr[U], xi[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const double* c = column(u);
+    xr[u] = c[(int64_t)r0 * n];
+    xi[u] = c[N + (int64_t)r0 * n];
+  }
+  const double* kp = kappa + (int64_t)slot * nm + j;
+  // the next row's loads: x-edges one row up, y-edges at the node and at its right neighbour
+  double lx[U][2], ly[U][2], lz[U][2], lk;
+  auto load = [&](int r) {
+    const int64_t o = (int64_t)r * n, ou = r + 1 < m ? o + n : 0;
+    lk = kp[o];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double* c = column(u);
+      lx[u][0] = c[ou];
+      lx[u][1] = c[N + ou];
+      ly[u][0] = c[nm + o];
+      ly[u][1] = c[N + nm + o];
+      lz[u][0] = c[nm + o + (jr - j)];
+      lz[u][1] = c[N + nm + o + (jr - j)];
+    }
+  };
+  auto stage = [&](int r) {   // row r from the loaded values
+    OneStage<NT>& b = st[r & 1];
+    const double ws = sqrt(lk * g.s);
+    const bool top = r + 1 >= m;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (NT % 2 && u == U - 1 && cc + 32 * u >= C::NC) continue;
+      Cx<double> up = {lx[u][0], lx[u][1]}, yr = {lz[u][0], lz[u][1]};
+      if (top) up = cmul(up, p.br, p.bi);
+      if (wrap) yr = cmul(yr, p.ar, p.ai);
+      const bool on = jok && cc + 32 * u < q;
+      const double fx = on ? sx : 0.0, fy = on ? sy : 0.0, fw = on ? ws : 0.0;
+      const double y0r = ly[u][0], y0i = ly[u][1];
+      const int c = cc + 32 * u;
+      b.v[0][jn][c] = double2{fx * fma(mb, up.re, ma * xr[u]), fx * fma(mb, up.im, ma * xi[u])};
+      b.v[1][jn][c] = double2{fy * fma(mb, yr.re, ma * y0r), fy * fma(mb, yr.im, ma * y0i)};
+      b.v[2][jn][c] = double2{fw * ((up.re - xr[u]) + (y0r - yr.re)), fw * ((up.im - xi[u]) + (y0i - yr.im))};
+      xr[u] = lx[u][0];
+      xi[u] = lx[u][1];
+      // (copied here and now: left to itself the compiler loads the next row elsewhere and moves it
+      // into place, waiting for it, as soon as it is issued)
+      asm volatile("" : "+v"(xr[u]), "+v"(xi[u]));
+    }
+  };
+  d4 acc[C::NACC];
+#pragma unroll
+  for (int i = 0; i < C::NACC; ++i) acc[i] = d4{0, 0, 0, 0};
+  load(r0);
+  stage(r0);
+  load(min(r0 + 1, r1 - 1));
+  auto products = [&](int r, auto half) {
+    one_wave<NT, decltype(half)::value>(
+        tw, [&](auto w, auto) { one_products<NT, decltype(w)::value>(st[r & 1], ks, lane, acc); });
+  };
+  // Row r + 1 is staged, and the loads of row r + 2 issued (the last row's again at the end), before
+  // the products of row r in the first half of the waves and after them in the second.  (A loop
+  // of its own for each half: a load under a condition would be waited for where its paths meet.)
+  auto rows = [&](auto half) {
+    for (int r = r0; r + 1 < r1; ++r) {
+      __syncthreads();   // row r is staged, and nobody reads the other buffer any more
+      if constexpr (!decltype(half)::value) {
+        stage(r + 1);
+        load(min(r + 2, r1 - 1));
+      }
+      products(r, half);
+      if constexpr (decltype(half)::value) {
+        stage(r + 1);
+        load(min(r + 2, r1 - 1));
+      }
+    }
+    __syncthreads();
+    products(r1 - 1, half);
+  };
+  if (wv < OW / 2) rows(std::integral_constant<int, 0>{});
+  else rows(std::integral_constant<int, 1>{});
+  if (C::KS > 1) __syncthreads();   // LDS is reused for the sums of the wave sets
+  double* pg = partial + ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * (int64_t)q * q * 4;
+  one_wave<NT, 2>(tw, [&](auto w, auto tasks) { one_store<NT, decltype(w)::value>(lds, ks, lane, q, pg, acc, tasks); });
+}
+
+// G_s, H_s from the partials of k_rr_one: 16 entries (i, j), i <= j, of G or H per workgroup, the
+// node ranges summed as in k_rr_reduce; entries below the diagonal are the mirrors.
+__global__ __launch_bounds__(256) void k_rr_one_reduce(const double* __restrict__ partial, int nblk, int q,
+                                                       double* __restrict__ G, double* __restrict__ H,
+                                                       const int* __restrict__ slots) {
+  __shared__ double2 part[16][17];
+  const int z = blockIdx.y;
+  const int64_t slot = slots ? slots[z] : z;
+  const int lo = threadIdx.x & 15, gq = threadIdx.x >> 4;
+  // blockIdx.x: product, row i, block of 16 columns
+  const int nbq = (q + 15) / 16;
+  const int prod = (int)blockIdx.x / (q * nbq), i = (int)blockIdx.x / nbq % q, j = (int)blockIdx.x % nbq * 16 + lo;
+  const bool in = j < q && i <= j, diag = i / 16 == j / 16;
+  const int64_t cnt = (int64_t)q * q * 2;   // complex entries of G and H
+  const double2* pz = reinterpret_cast<const double2*>(partial) + (int64_t)z * nblk * cnt + (int64_t)prod * q * q;
+  const int b0 = (int)((int64_t)nblk * gq / 16), b1 = (int)((int64_t)nblk * (gq + 1) / 16);
+  double sr = 0, si = 0;
+  if (in)
+    for (int b = b0; b < b1; ++b) {
+      const double2* e = pz + (int64_t)b * cnt;
+      const double2 v = e[(int64_t)i * q + j];
+      sr += v.x;
+      si += diag ? v.y - e[(int64_t)j * q + i].y : v.y;
+    }
+  part[gq][lo] = double2{sr, si};
+  __syncthreads();
+  if (gq == 0 && in) {
+    double2 t = part[0][lo];
+    for (int k = 1; k < 16; ++k) {
+      t.x += part[k][lo].x;
+      t.y += part[k][lo].y;
+    }
+    if (i == j) t.y = 0.0;
+    double2* out = reinterpret_cast<double2*>(prod ? H : G) + slot * q * q;
+    out[(int64_t)i * q + j] = t;
+    if (i != j) out[(int64_t)j * q + i] = double2{t.x, -t.y};
+  }
+}
+
 #undef BL_MFMA
 
 // G_s, H_s = sums over the node ranges of launch entry z: 16 entries per block, the ranges
@@ -674,6 +1051,34 @@ int rr_blocks(int64_t nm) {
 int rr_gram(View<const double> S, int q, const double* kappa, const Geo& g, const Phase* ph,
             double* partial, int64_t partial_cap, double* G, double* H, int tile, const Launch& L) {
   if (L.nact <= 0) return 0;
+  if (q <= 16 * kOneTiles) {
+    const RRGrid grd = rr_mfma_grid(g);
+    if ((int64_t)grd.blocks * q * q * 4 * L.nact > partial_cap) return -1;
+    auto launch = [&](auto ntt) {
+      constexpr int NT = decltype(ntt)::value;
+      using C = OneConf<NT>;
+      const size_t stage = 2 * sizeof(OneStage<NT>), red = C::KS > 1 ? (size_t)C::TW * C::NACC * 4 * 64 * sizeof(double) : 0;
+      const size_t lds = stage > red ? stage : red;
+      static const bool attr = [&] {   // once per instantiation, thread-safely
+        (void)hipFuncSetAttribute((const void*)k_rr_one<NT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        return true;
+      }();
+      (void)attr;
+      k_rr_one<NT><<<dim3((unsigned)grd.blocks, 1u, (unsigned)L.nact), 64 * OW, lds, L.st>>>(
+          S, q, kappa, g, ph, grd.slices, grd.band, partial, L.slots);
+    };
+    switch ((q + 15) / 16) {
+      case 1: launch(std::integral_constant<int, 1>{}); break;
+      case 2: launch(std::integral_constant<int, 2>{}); break;
+      case 3: launch(std::integral_constant<int, 3>{}); break;
+      case 4: launch(std::integral_constant<int, 4>{}); break;
+      case 5: launch(std::integral_constant<int, 5>{}); break;
+      default: launch(std::integral_constant<int, 6>{}); break;
+    }
+    k_rr_one_reduce<<<dim3((unsigned)(2 * q * ((q + 15) / 16)), (unsigned)L.nact), 256, 0, L.st>>>(partial, grd.blocks,
+                                                                                                  q, G, H, L.slots);
+    return 0;
+  }
   if (q <= kMfmaGroups * MQ) {
     const RRGrid grd = rr_mfma_grid(g);
     const int nb = grd.blocks;
