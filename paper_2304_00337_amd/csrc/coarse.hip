@@ -4,8 +4,25 @@
 // solve, prolongation and post-smoothing on every remaining level — runs in one workgroup
 // per column, with all levels' vectors in LDS and a barrier between dependent passes.  The
 // per-point bodies are those of the per-level kernels (stencil_ops.h) and the coarsest solve
-// sums in the same order as k_dense_apply, so a fused cycle reproduces the per-level one bit
-// for bit.
+// is k_dense_apply's (dense_row), so a fused cycle reproduces the per-level one bit for bit.
+//
+// What bounds it: a chain of some 40 short dependent passes, one workgroup per column, so the
+// latency of a pass is what counts.  Therefore
+//  * a thread owns a coarse node of a level, that is the 2 x 2 fine nodes around it, in every pass:
+//    the rows and columns that its passes read (wrapped at the period) are worked out once per
+//    level, and its patches' coefficients are loaded once per level, ahead of their use, and kept
+//    for the sweeps and the residual;
+//  * a pass loads its neighbourhood first and then applies the Bloch phases of a crossing, in one
+//    branch per direction that only the threads at the period's edge take;
+//  * where the threads suffice, two neighbouring lanes share a coarse node, one for the real and one
+//    for the imaginary parts (the stencils are real; only the phases mix them): twice the waves and
+//    half the instructions of each;
+//  * values are interleaved complex and the even and the odd columns of a row stand apart, so that
+//    the lanes of a colour read consecutive words;
+//  * in the dense solve a lane takes a row and a wave an eighth of its terms, 16 loads in flight.
+// From a 32 x 32 level down (FP64): 28 us for edges and 15 us for nodes, against 76 and 41 us
+// with every read wrapped and phased by itself, coefficients loaded per pass and one thread per row of
+// the dense solve.
 #include "stencil_ops.h"
 
 #include <cstdlib>
@@ -16,10 +33,13 @@ namespace bl {
 
 namespace {
 
-// Threads per fused workgroup.  Only one workgroup per column runs, so the cycle is latency
-// bound: more threads shorten every pass (a 64 x 64 nodal colour pass is one node per thread
-// at 1024), at the price of slightly dearer barriers.
-constexpr int kFusedMaxThreads = 1024;
+// Largest workgroups: the registers that the coefficients take (edges) or the dense solve's loads
+// (FP64) allow no more waves; the LDS that a cycle takes (at least 112 bytes per node of its first
+// level for FP64 edges, 56 for FP32 edges and FP64 nodes, of 160 KB) keeps the coarse nodes below these.
+template <typename T, int LP>
+constexpr int edge_threads() { return sizeof(T) == 8 || LP == 2 ? 512 : 768; }
+template <typename T, int LP>
+constexpr int nodal_threads() { return sizeof(T) == 4 ? 1024 : LP == 2 ? 512 : 768; }
 
 template <typename T>
 __device__ __forceinline__ const T* pickp(const double* a, const float* b);
@@ -28,224 +48,492 @@ __device__ __forceinline__ const double* pickp<double>(const double* a, const fl
 template <>
 __device__ __forceinline__ const float* pickp<float>(const double*, const float* b) { return b; }
 
-// LDS vector `which` (0 = iterate x, 1 = right-hand side b, 2 = residual r) of fused level
-// l: per level l < nlev-1 the three vectors (2 ne or 2 nm values each), on the coarsest x
-// and b.  Offsets are recomputed from the cycle description (no pointer tables in scratch).
-template <typename T>
-__device__ __forceinline__ T* lds_vec(T* base, const CoarseCycle& C, bool edge, int l, int which) {
-  int64_t off = 0;
-  for (int i = 0; i < l; ++i) {
-    const int64_t len = 2 * (edge ? C.L[i].g.ne : C.L[i].g.nm);
-    off += len * (i + 1 < C.nlev ? 3 : 2);
+// A vector of a level in LDS: per component (two for edges, one for nodes) a plane of n x m complex
+// values; a row holds its even columns first, then the odd ones.  With LP = 2 lanes per coarse node
+// each lane handles its part (0: real, 1: imaginary), passed around in the .re of a value.
+template <typename T, int LP>
+struct Plane {
+  T* q;
+  int H, W, plane, part;
+  __device__ __forceinline__ Plane(T* base, const Geo& g)
+      : q(base), H((g.n + 1) >> 1), W(2 * H), plane(W * g.m), part(LP == 2 ? (int)threadIdx.x & 1 : 0) {}
+  __device__ __forceinline__ int index(int j1, int j2) const { return j2 * W + (j1 & 1) * H + (j1 >> 1); }
+  __device__ __forceinline__ Cx<T> load(int c, int i) const {
+    const T* v = q + 2 * (c * plane + i);
+    if (LP == 2) return {v[part], 0};
+    return {v[0], v[1]};
   }
-  return base + off + which * 2 * (edge ? C.L[l].g.ne : C.L[l].g.nm);
-}
-
-// x = Inv b for the Hermitian inverse of one slot (row i read as the conjugate of column i).
-template <typename T>
-__device__ void dense_solve(const T* inv, int64_t n, const T* b, T* x) {
-  for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-    T sr = 0, si = 0;
-    // (unrolled: the loads of several terms are in flight; the summation order is unchanged)
-#pragma unroll 8
-    for (int64_t l = 0; l < n; ++l) {
-      const T ar = inv[2 * (l * n + i)], ai = -inv[2 * (l * n + i) + 1];
-      const T br = b[l], bi = b[n + l];
-      sr += ar * br - ai * bi;
-      si += ar * bi + ai * br;
+  __device__ __forceinline__ void store(int c, int i, Cx<T> v) const {
+    T* d = q + 2 * (c * plane + i);
+    if (LP == 2) {
+      d[part] = v.re;
+    } else {
+      d[0] = v.re;
+      d[1] = v.im;
     }
-    x[i] = sr;
-    x[n + i] = si;
+  }
+};
+// Values of a column in memory: N real, then N imaginary parts.
+template <typename T, int LP>
+__device__ __forceinline__ Cx<T> planar(const T* c, int64_t N, int i) {
+  if (LP == 2) return {c[(threadIdx.x & 1) * N + i], 0};
+  return {c[i], c[N + i]};
+}
+template <typename T, int LP>
+__device__ __forceinline__ void set_planar(T* c, int64_t N, int i, Cx<T> v) {
+  if (LP == 2) {
+    c[(threadIdx.x & 1) * N + i] = v.re;
+  } else {
+    c[i] = v.re;
+    c[N + i] = v.im;
+  }
+}
+// v times the phase ar + i ai (both lanes of a pair are here together)
+template <typename T, int LP>
+__device__ __forceinline__ Cx<T> rotate(Cx<T> v, T ar, T ai) {
+  if (LP == 1) return cmul(v, ar, ai);
+  const T other = lane_xor1(v.re), own = v.re * ar, mix = other * ai;
+  return {(threadIdx.x & 1) ? mix + own : own - mix, 0};
+}
+
+// A thread's coarse node (a, b) of a level (on = false beyond the last): LDS rows and columns
+// 2 b - 1 .. 2 b + 2 and 2 a - 1 .. 2 a + 2 of a fine plane, wrapped at the period, and whether the
+// first and last of them are across it.
+struct Site {
+  int a, b, n, row[4], col[4];
+  bool on, xl, xh, yl, yh;
+  template <int LP>
+  __device__ __forceinline__ void place(const Geo& g) {
+    const int nh = g.n >> 1, mh = g.m >> 1, t = (int)threadIdx.x / LP;
+    on = t < nh * mh;
+    split_index(on ? t : 0, nh, a, b);
+    n = g.n;
+    xl = a == 0;
+    xh = a == nh - 1;
+    yl = b == 0;
+    yh = b == mh - 1;
+    col[0] = nh + (xl ? nh - 1 : a - 1);
+    col[1] = a;
+    col[2] = nh + a;
+    col[3] = xh ? 0 : a + 1;
+    row[0] = (yl ? g.m - 1 : 2 * b - 1) * n;
+    row[1] = 2 * b * n;
+    row[2] = row[1] + n;
+    row[3] = yh ? 0 : row[2] + n;
+  }
+  // the fine node of colour c in a planar column
+  __device__ __forceinline__ int node(int c) const { return (2 * b + (c >> 1)) * n + 2 * a + (c & 1); }
+  // Runs f(integral_constant<int, c>) for the four colours c in order, or in reverse.  The rows are
+  // made opaque before each, so that the compiler does not keep all colours' addresses in registers.
+  template <bool REV = false, typename F>
+  __device__ __forceinline__ void each_colour(const F& f) {
+    auto one = [&](auto c) {
+      asm volatile("" : "+v"(row[0]), "+v"(row[1]), "+v"(row[2]), "+v"(row[3]));
+      f(c);
+    };
+    one(std::integral_constant<int, REV ? 3 : 0>{});
+    one(std::integral_constant<int, REV ? 2 : 1>{});
+    one(std::integral_constant<int, REV ? 1 : 2>{});
+    one(std::integral_constant<int, REV ? 0 : 3>{});
+  }
+};
+
+// The values around the fine node of colour C of a site, in Bloch-extended coordinates (as fetch():
+// the x phase first), for the shared point bodies.  What a body does not read is not loaded.
+template <typename T, int LP, int C, int COMPS>
+struct Near {
+  static constexpr int PX = C & 1, PY = C >> 1;
+  const Plane<T, LP>& X;
+  const Site& s;
+  Cx<T> v[COMPS][3][3], raw[2];   // raw: the stored x-edge (-1, 0) and y-edge (0, -1)
+  __device__ __forceinline__ int at(int d1, int d2) const { return s.row[PY + d2 + 1] + s.col[PX + d1 + 1]; }
+  __device__ __forceinline__ Near(const Plane<T, LP>& x, const Site& site) : X(x), s(site) {
+#pragma unroll
+    for (int c = 0; c < COMPS; ++c)
+#pragma unroll
+      for (int d2 = -1; d2 <= 1; ++d2)
+#pragma unroll
+        for (int d1 = -1; d1 <= 1; ++d1) v[c][d2 + 1][d1 + 1] = X.load(c, at(d1, d2));
+    raw[0] = v[0][1][0];
+    raw[1] = v[COMPS - 1][0][1];
+  }
+  // the phases of the values across the period in x, in y (callers branch on the site's flags)
+  __device__ __forceinline__ void cross_x(const Ph<T>& p) {
+#pragma unroll
+    for (int c = 0; c < COMPS; ++c)
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+        v[c][d][PX ? 2 : 0] = rotate<T, LP>(v[c][d][PX ? 2 : 0], p.ar, PX ? p.ai : -p.ai);
+  }
+  __device__ __forceinline__ void cross_y(const Ph<T>& p) {
+#pragma unroll
+    for (int c = 0; c < COMPS; ++c)
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+        v[c][PY ? 2 : 0][d] = rotate<T, LP>(v[c][PY ? 2 : 0][d], p.br, PY ? p.bi : -p.bi);
+  }
+  __device__ __forceinline__ bool at_x() const { return PX ? s.xh : s.xl; }
+  __device__ __forceinline__ bool at_y() const { return PY ? s.yh : s.yl; }
+  __device__ __forceinline__ Near& cross(const Ph<T>& p) {
+    if (at_x()) cross_x(p);
+    if (at_y()) cross_y(p);
+    return *this;
+  }
+};
+template <typename T, int LP, int C>
+struct EdgesNear : Near<T, LP, C, 2> {
+  using N = Near<T, LP, C, 2>;
+  const Ph<T>& p;
+  __device__ __forceinline__ EdgesNear(const Plane<T, LP>& x, const Site& site, const Ph<T>& ph) : N(x, site), p(ph) {}
+  __device__ __forceinline__ Cx<T> get(int c, int d1, int d2) const { return N::v[c][d2 + 1][d1 + 1]; }
+  // as add_ext(): a value written one period back is stored times alpha (beta)
+  __device__ __forceinline__ void add(int c, int d1, int d2, Cx<T> u) const {
+    if (d1 < 0 && N::PX == 0 && N::s.xl) u = rotate<T, LP>(u, p.ar, p.ai);
+    if (d2 < 0 && N::PY == 0 && N::s.yl) u = rotate<T, LP>(u, p.br, p.bi);
+    const Cx<T> old = c == 0 && d1 < 0 ? N::raw[0] : c == 1 && d2 < 0 ? N::raw[1] : get(c, d1, d2);
+    N::X.store(c, N::at(d1, d2), old + u);
+  }
+};
+template <typename T, int LP, int C>
+struct NodesNear : Near<T, LP, C, 1> {
+  using N = Near<T, LP, C, 1>;
+  __device__ __forceinline__ NodesNear(const Plane<T, LP>& x, const Site& site, const Ph<T>& p) : N(x, site) { N::cross(p); }
+  __device__ __forceinline__ Cx<T> get(int d1, int d2) const { return N::v[0][d2 + 1][d1 + 1]; }
+};
+
+// The coefficients of a thread's four patches: kappa of the 3 x 3 cells around its fine nodes, and
+// the patch inverses (colour c: node (2 a + (c & 1), 2 b + (c >> 1))).
+template <typename T>
+struct PatchCoef {
+  T k[3][3], w[4][kPatchW];
+};
+template <typename T>
+__device__ __forceinline__ void load_coef(const CoarseLevel& lv, int slot, const Site& s, PatchCoef<T>& K) {
+  struct alignas(2 * sizeof(T)) Pair {
+    T x, y;
+  };
+  static_assert(kPatchW % 2 == 0, "pairs of entries");
+  const int n = lv.g.n, m = lv.g.m, a = s.a, b = s.b;
+  const Pair* si = reinterpret_cast<const Pair*>(pickp<T>(lv.si64, lv.si32) + kPatchW * (int64_t)slot * lv.g.nm);
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int u = 0; u < kPatchW / 2; ++u) {
+      const Pair v = si[kPatchW / 2 * s.node(c) + u];
+      K.w[c][2 * u] = v.x;
+      K.w[c][2 * u + 1] = v.y;
+    }
+  const double* k64 = lv.k64 + (int64_t)slot * lv.g.nm;
+  const float* k32 = lv.k32 + (int64_t)slot * lv.g.nm;
+  const int x[3] = {a > 0 ? 2 * a - 1 : n - 1, 2 * a, 2 * a + 1}, y[3] = {b > 0 ? 2 * b - 1 : m - 1, 2 * b, 2 * b + 1};
+#pragma unroll
+  for (int v = 0; v < 3; ++v)
+#pragma unroll
+    for (int u = 0; u < 3; ++u) K.k[v][u] = kap<T>(k64, k32, y[v] * n + x[u]);
+}
+
+template <typename T, int LP, bool BWD>
+__device__ __forceinline__ void edge_sweep(const Plane<T, LP>& X, const Plane<T, LP>& B, const CoarseLevel& lv,
+                                           const PatchCoef<T>& K, Site& site, const Ph<T>& p, T mu) {
+  const T s = (T)lv.g.s, mmx = mu * (T)lv.g.mx, mmy = mu * (T)lv.g.my;
+  site.each_colour<BWD>([&](auto colour) {
+    constexpr int c = decltype(colour)::value, px = c & 1, py = c >> 1;
+    if (site.on) {
+      EdgesNear<T, LP, c> x(X, site, p), b(B, site, p);
+      if (x.at_x()) {
+        x.cross_x(p);
+        if (!px) b.cross_x(p);
+      }
+      if (x.at_y()) {
+        x.cross_y(p);
+        if (!py) b.cross_y(p);
+      }
+      patch_update<T>(x, b, K.k[py + 1][px + 1], K.k[py + 1][px], K.k[py][px], K.k[py][px + 1], K.w[c], s, mmx, mmy);
+    }
+    __syncthreads();
+  });
+}
+
+// The coarsest solve, x = Inv b, over the whole workgroup: a wave sums a part of 64 rows at a time
+// into `part` (room for `groups` groups of 64 rows), then a thread combines and stores a row.
+template <typename T, typename Store>
+__device__ __forceinline__ void dense_solve(const T* inv, int n, const T* b, T* part, int groups, const Store& store) {
+  const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int waves = (int)blockDim.x >> 6, all = (n + 63) >> 6;
+#pragma unroll 1
+  for (int g0 = 0; g0 < all; g0 += groups) {
+    const int ng = groups < all - g0 ? groups : all - g0;
+#pragma unroll 1
+    for (int t = wave; t < ng * kDenseParts; t += waves) {
+      const int k = t % kDenseParts, r = t / kDenseParts * 64 + lane, i = g0 * 64 + r;
+      if (i < n) {
+        const Cx<T> v = dense_part<T>(inv, n, b, i, n * k / kDenseParts, n * (k + 1) / kDenseParts);
+        part[(2 * k) * (ng * 64) + r] = v.re;
+        part[(2 * k + 1) * (ng * 64) + r] = v.im;
+      }
+    }
+    __syncthreads();
+    for (int r = (int)threadIdx.x; r < ng * 64 && g0 * 64 + r < n; r += (int)blockDim.x)
+      store(g0 * 64 + r, Cx<T>{dense_sum([&](int k) { return part[2 * k * (ng * 64) + r]; }),
+                               dense_sum([&](int k) { return part[(2 * k + 1) * (ng * 64) + r]; })});
+    __syncthreads();
   }
 }
 
-template <typename T>
-__device__ void edge_colour(const CoarseCycle& C, int l, int slot, T* x, const T* b, int colour, T mu,
-                            const Ph<T>& p) {
-  const CoarseLevel& lv = C.L[l];
-  const Geo& g = lv.g;
-  const int n = g.n, m = g.m, nh = n >> 1, mh = m >> 1;
-  const int64_t nm = g.nm;
-  const double* k64 = lv.k64 + (int64_t)slot * nm;
-  const float* k32 = lv.k32 + (int64_t)slot * nm;
-  const T s = (T)g.s, mmx = mu * (T)g.mx, mmy = mu * (T)g.my;
-  for (int t = threadIdx.x; t < nh * mh; t += blockDim.x) {
-    const int p1 = 2 * (t % nh) + (colour & 1);
-    const int p2 = 2 * (t / nh) + (colour >> 1);
-    const int p1m = wrapi(p1 - 1, n), p2m = wrapi(p2 - 1, m);
-    const T kne = kap<T>(k64, k32, (int64_t)p2 * n + p1);
-    const T knw = kap<T>(k64, k32, (int64_t)p2 * n + p1m);
-    const T ksw = kap<T>(k64, k32, (int64_t)p2m * n + p1m);
-    const T kse = kap<T>(k64, k32, (int64_t)p2m * n + p1);
-    const T* si = pickp<T>(lv.si64, lv.si32) + kPatchW * ((int64_t)slot * nm + (int64_t)p2 * n + p1);
-    edge_patch_gs<T>(x, b, g.ne, n, m, nm, p1, p2, kne, knw, ksw, kse, si, s, mmx, mmy, p);
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kFusedMaxThreads) void k_edge_vcycle_fused(View<const T> bv, View<T> xv, CoarseCycle C,
-                                                           const Phase* __restrict__ phs,
-                                                           const double* __restrict__ mus,
-                                                           const int* __restrict__ slots, int ncps) {
+template <typename T, int LP>
+__global__ __launch_bounds__((edge_threads<T, LP>())) void k_edge_vcycle_fused(
+    View<const T> bv, View<T> xv, CoarseCycle C, const Phase* __restrict__ phs, const double* __restrict__ mus,
+    const int* __restrict__ slots, int ncps) {
+  using P1 = Plane<T, 1>;
+  using PL = Plane<T, LP>;
   extern __shared__ unsigned char lds_raw[];
   const int zi = (int)blockIdx.x / ncps;
   const int slot = slots ? slots[zi] : zi;
   const SJ sj{slot, (int)blockIdx.x % ncps};
+  T* const base = reinterpret_cast<T*>(lds_raw);
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const int last = C.nlev - 1;
+  const T* const inv = static_cast<const T*>(C.inv) + (int64_t)slot * C.nc * C.nc * 2;
+  Site site;
+  PatchCoef<T> K;
+  site.place<LP>(C.L[0].g);
+  {
+    const Geo& g = C.L[0].g;
+    const T* bg = colp(bv, sj, g.ne);
+    const PL B(base + C.bo[0], g);
+    Cx<T> bx[4], by[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      bx[c] = planar<T, LP>(bg, g.ne, site.node(c));
+      by[c] = planar<T, LP>(bg + g.nm, g.ne, site.node(c));
+    }
+    load_coef<T>(C.L[0], slot, site, K);
+    for (int l = 0; l < last; ++l) {
+      T* x = base + C.xo[l];
+      const int len = 4 * (int)C.L[l].g.nm;
+      for (int i = tid; i < len; i += nt) x[i] = (T)0;
+    }
+    if (site.on)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        B.store(0, site.row[(c >> 1) + 1] + site.col[(c & 1) + 1], bx[c]);
+        B.store(1, site.row[(c >> 1) + 1] + site.col[(c & 1) + 1], by[c]);
+      }
+  }
   const Ph<T> p = cast_phase<T>(phs[slot]);
   const T mu = (T)mus[slot];
-  T* const base = reinterpret_cast<T*>(lds_raw);
-  const int tid = threadIdx.x, nt = blockDim.x;
-  {
-    const T* bg = colp(bv, sj, C.L[0].g.ne);
-    T* b0 = lds_vec(base, C, true, 0, 1);
-    for (int64_t i = tid; i < 2 * C.L[0].g.ne; i += nt) b0[i] = bg[i];
-  }
   __syncthreads();
-  const int last = C.nlev - 1;
+#pragma unroll 1
   for (int l = 0; l < last; ++l) {
     const Geo& g = C.L[l].g;
-    const int64_t N = g.ne;
-    T* x = lds_vec(base, C, true, l, 0);
-    const T* b = lds_vec(base, C, true, l, 1);
-    T* r = lds_vec(base, C, true, l, 2);
-    for (int64_t i = tid; i < 2 * N; i += nt) x[i] = (T)0;
-    __syncthreads();
-    for (int it = 0; it < C.nu_pre; ++it)
-      for (int c = 0; c < 4; ++c) {
-        edge_colour<T>(C, l, slot, x, b, c, mu, p);
-        __syncthreads();
-      }
-    const double* k64 = C.L[l].k64 + (int64_t)slot * g.nm;
-    const float* k32 = C.L[l].k32 + (int64_t)slot * g.nm;
-    for (int64_t d = tid; d < N; d += nt) {
-      Cx<T> Au, Mu;
-      edge_AM<T, T>(x, N, g.n, g.m, g.nm, d, [&](int64_t i) { return kap<T>(k64, k32, i); }, (T)g.s, (T)g.mx,
-                    (T)g.my, p, Au, Mu);
-      const Cx<T> v = Cx<T>{b[d], b[N + d]} - (Au + (mu * Mu));
-      r[d] = v.re;
-      r[N + d] = v.im;
+    const Geo& gc = C.L[l + 1].g;
+    const PL X(base + C.xo[l], g), B(base + C.bo[l], g), R(base + C.ro, g);
+#pragma unroll 1
+    for (int it = 0; it < C.nu_pre; ++it) edge_sweep<T, LP, false>(X, B, C.L[l], K, site, p, mu);
+    const T s = (T)g.s, mx = (T)g.mx, my = (T)g.my;
+    if (site.on)
+      site.each_colour([&](auto colour) {
+        constexpr int c = decltype(colour)::value, px = c & 1, py = c >> 1;
+        EdgesNear<T, LP, c> x(X, site, p);
+        x.cross(p);
+        const int i = x.at(0, 0);
+        Cx<T> Au, Mu;
+        edge_AM_acc<T>(x, 0, K.k[py][px + 1], K.k[py + 1][px + 1], s, mx, Au, Mu);
+        R.store(0, i, B.load(0, i) - (Au + (mu * Mu)));
+        edge_AM_acc<T>(x, 1, K.k[py + 1][px + 1], K.k[py + 1][px], s, my, Au, Mu);
+        R.store(1, i, B.load(1, i) - (Au + (mu * Mu)));
+      });
+    // the next level's coefficients are on their way while this one is restricted
+    const Site fine = site;
+    if (l + 1 < last) {
+      site.place<LP>(gc);
+      load_coef<T>(C.L[l + 1], slot, site, K);
     }
     __syncthreads();
-    const Geo& gc = C.L[l + 1].g;
-    T* bc = lds_vec(base, C, true, l + 1, 1);
-    for (int64_t d = tid; d < gc.ne; d += nt) {
-      const Cx<T> v = edge_restrict_at<T>(r, g, gc, d, p);
-      bc[d] = v.re;
-      bc[gc.ne + d] = v.im;
+    if (fine.on) {
+      EdgesNear<T, LP, 0> r(R, fine, p);
+      r.cross(p);
+      const Cx<T> vx = edge_restrict_acc<T>(r, 0), vy = edge_restrict_acc<T>(r, 1);
+      T* bc = base + C.bo[l + 1];
+      const PL Bc(bc, gc);
+      if (l + 1 < last) {
+        Bc.store(0, Bc.index(fine.a, fine.b), vx);
+        Bc.store(1, Bc.index(fine.a, fine.b), vy);
+      } else {
+        set_planar<T, LP>(bc, gc.ne, fine.b * gc.n + fine.a, vx);
+        set_planar<T, LP>(bc + gc.nm, gc.ne, fine.b * gc.n + fine.a, vy);
+      }
     }
     __syncthreads();
   }
-  dense_solve<T>(static_cast<const T*>(C.inv) + (int64_t)slot * C.nc * C.nc * 2, C.nc, lds_vec(base, C, true, last, 1),
-                 lds_vec(base, C, true, last, 0));
-  __syncthreads();
+  {
+    const Geo& g = C.L[last].g;
+    const P1 X(base + C.xo[last], g);
+    const int nm = (int)g.nm;
+    dense_solve<T>(inv, (int)C.nc, base + C.bo[last],
+                   base + C.ro, C.groups, [&](int i, Cx<T> v) {
+                     const int c = i >= nm ? 1 : 0;
+                     int j1, j2;
+                     split_index(i - c * nm, g.n, j1, j2);
+                     X.store(c, X.index(j1, j2), v);
+                   });
+  }
+#pragma unroll 1
   for (int l = last - 1; l >= 0; --l) {
     const Geo& g = C.L[l].g;
-    const Geo& gc = C.L[l + 1].g;
-    T* x = lds_vec(base, C, true, l, 0);
-    const T* xc = lds_vec(base, C, true, l + 1, 0);
-    for (int64_t d = tid; d < g.ne; d += nt) {
-      const Cx<T> v = edge_prolong_at<T>(xc, gc, g, d, p);
-      x[d] += v.re;
-      x[g.ne + d] += v.im;
+    const PL X(base + C.xo[l], g), B(base + C.bo[l], g), Xc(base + C.xo[l + 1], C.L[l + 1].g);
+    if (l < last - 1) {
+      site.place<LP>(g);
+      load_coef<T>(C.L[l], slot, site, K);
+    }
+    if (site.on) {
+      const int a = site.a, b = site.b, i = Xc.index(a, b);
+      const Cx<T> x00 = Xc.load(0, i), y00 = Xc.load(1, i);
+      Cx<T> x01 = Xc.load(0, Xc.index(a, site.yh ? 0 : b + 1)), y10 = Xc.load(1, Xc.index(site.xh ? 0 : a + 1, b));
+      if (site.xh) y10 = rotate<T, LP>(y10, p.ar, p.ai);
+      if (site.yh) x01 = rotate<T, LP>(x01, p.br, p.bi);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int i = site.row[(c >> 1) + 1] + site.col[(c & 1) + 1];
+        X.store(0, i, X.load(0, i) + edge_prolong_combine<T>(x00, x01, c >> 1));
+        X.store(1, i, X.load(1, i) + edge_prolong_combine<T>(y00, y10, c & 1));
+      }
     }
     __syncthreads();
-    const T* b = lds_vec(base, C, true, l, 1);
-    for (int it = 0; it < C.nu_post; ++it)
-      for (int c = 3; c >= 0; --c) {
-        edge_colour<T>(C, l, slot, x, b, c, mu, p);
-        __syncthreads();
-      }
+#pragma unroll 1
+    for (int it = 0; it < C.nu_post; ++it) edge_sweep<T, LP, true>(X, B, C.L[l], K, site, p, mu);
   }
-  T* xg = colp(xv, sj, C.L[0].g.ne);
-  const T* x0 = lds_vec(base, C, true, 0, 0);
-  for (int64_t i = tid; i < 2 * C.L[0].g.ne; i += nt) xg[i] = x0[i];
+  const Geo& g = C.L[0].g;
+  T* xg = colp(xv, sj, g.ne);
+  const PL X(base + C.xo[0], g);
+  if (site.on)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int i = site.row[(c >> 1) + 1] + site.col[(c & 1) + 1];
+      set_planar<T, LP>(xg, g.ne, site.node(c), X.load(0, i));
+      set_planar<T, LP>(xg + g.nm, g.ne, site.node(c), X.load(1, i));
+    }
 }
 
-template <typename T>
-__device__ void nodal_colour(const Geo& g, T* x, const T* b, int colour, const NodalStencil& s, const Ph<T>& p) {
-  const int nh = g.n >> 1, mh = g.m >> 1;
-  const int64_t N = g.nm;
-  const T inv = (T)1 / (T)s.c0;
-  for (int t = threadIdx.x; t < nh * mh; t += blockDim.x) {
-    const int p1 = 2 * (t % nh) + (colour & 1);
-    const int p2 = 2 * (t / nh) + (colour >> 1);
-    const int64_t i = (int64_t)p2 * g.n + p1;
-    const Cx<T> r = Cx<T>{b[i], b[N + i]} - nodal_stencil<T>(x, N, g.n, g.m, p1, p2, s, p);
-    x[i] += inv * r.re;
-    x[N + i] += inv * r.im;
-  }
+template <typename T, int LP, bool BWD>
+__device__ __forceinline__ void nodal_sweep(const Plane<T, LP>& X, const Cx<T> (&rhs)[4], const NodalStencil& st,
+                                            Site& site, const Ph<T>& p) {
+  const T inv = (T)1 / (T)st.c0;
+  site.each_colour<BWD>([&](auto colour) {
+    constexpr int c = decltype(colour)::value;
+    if (site.on) {
+      const NodesNear<T, LP, c> x(X, site, p);
+      const Cx<T> r = rhs[c] - nodal_stencil_at<T>(x, st), u = x.get(0, 0);
+      X.store(0, x.at(0, 0), Cx<T>{u.re + inv * r.re, u.im + inv * r.im});
+    }
+    __syncthreads();
+  });
 }
 
-template <typename T>
-__global__ __launch_bounds__(kFusedMaxThreads) void k_nodal_vcycle_fused(View<const T> bv, View<T> xv, CoarseCycle C,
-                                                            const Phase* __restrict__ phs,
-                                                            const int* __restrict__ slots, int ncps) {
+template <typename T, int LP>
+__global__ __launch_bounds__((nodal_threads<T, LP>())) void k_nodal_vcycle_fused(View<const T> bv, View<T> xv, CoarseCycle C,
+                                                                                 const Phase* __restrict__ phs,
+                                                                                 const int* __restrict__ slots, int ncps) {
+  using P1 = Plane<T, 1>;
+  using PL = Plane<T, LP>;
   extern __shared__ unsigned char lds_raw[];
   const int zi = (int)blockIdx.x / ncps;
   const int slot = slots ? slots[zi] : zi;
   const SJ sj{slot, (int)blockIdx.x % ncps};
-  const Ph<T> p = cast_phase<T>(phs[slot]);
   T* const base = reinterpret_cast<T*>(lds_raw);
   const int tid = threadIdx.x, nt = blockDim.x;
-  {
-    const T* bg = colp(bv, sj, C.L[0].g.nm);
-    T* b0 = lds_vec(base, C, false, 0, 1);
-    for (int64_t i = tid; i < 2 * C.L[0].g.nm; i += nt) b0[i] = bg[i];
-  }
-  __syncthreads();
   const int last = C.nlev - 1;
+  const T* const inv = static_cast<const T*>(C.inv) + (int64_t)slot * C.nc * C.nc * 2;
+  Site site;
+  // the right-hand side is read at the thread's own nodes only: plain planes, and registers
+  Cx<T> rhs[4];
+  auto load_rhs = [&](const T* src, const Geo& g) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) rhs[c] = planar<T, LP>(src, g.nm, site.node(c));
+  };
+  site.place<LP>(C.L[0].g);
+  load_rhs(colp(bv, sj, C.L[0].g.nm), C.L[0].g);
+  for (int l = 0; l < last; ++l) {
+    T* x = base + C.xo[l];
+    const int len = 2 * (int)C.L[l].g.nm;
+    for (int i = tid; i < len; i += nt) x[i] = (T)0;
+  }
+  if (site.on)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) set_planar<T, LP>(base + C.bo[0], C.L[0].g.nm, site.node(c), rhs[c]);
+  const Ph<T> p = cast_phase<T>(phs[slot]);
+  __syncthreads();
+#pragma unroll 1
   for (int l = 0; l < last; ++l) {
     const Geo& g = C.L[l].g;
-    const int64_t N = g.nm;
-    T* x = lds_vec(base, C, false, l, 0);
-    const T* b = lds_vec(base, C, false, l, 1);
-    T* r = lds_vec(base, C, false, l, 2);
-    for (int64_t i = tid; i < 2 * N; i += nt) x[i] = (T)0;
-    __syncthreads();
-    for (int it = 0; it < C.nu_pre; ++it)
-      for (int c = 0; c < 4; ++c) {
-        nodal_colour<T>(g, x, b, c, C.ns, p);
-        __syncthreads();
-      }
-    for (int64_t d = tid; d < N; d += nt) {
-      const Cx<T> v = Cx<T>{b[d], b[N + d]} - nodal_stencil<T>(x, N, g.n, g.m, (int)(d % g.n), (int)(d / g.n), C.ns, p);
-      r[d] = v.re;
-      r[N + d] = v.im;
-    }
-    __syncthreads();
     const Geo& gc = C.L[l + 1].g;
-    T* bc = lds_vec(base, C, false, l + 1, 1);
-    for (int64_t d = tid; d < gc.nm; d += nt) {
-      const Cx<T> v = nodal_restrict_at<T>(r, g, gc, d, p);
-      bc[d] = v.re;
-      bc[gc.nm + d] = v.im;
+    const PL X(base + C.xo[l], g), R(base + C.ro, g);
+    if (l > 0) {
+      site.place<LP>(g);
+      load_rhs(base + C.bo[l], g);
+    }
+#pragma unroll 1
+    for (int it = 0; it < C.nu_pre; ++it) nodal_sweep<T, LP, false>(X, rhs, C.ns, site, p);
+    if (site.on)
+      site.each_colour([&](auto colour) {
+        constexpr int c = decltype(colour)::value;
+        const NodesNear<T, LP, c> x(X, site, p);
+        R.store(0, x.at(0, 0), rhs[c] - nodal_stencil_at<T>(x, C.ns));
+      });
+    __syncthreads();
+    if (site.on) {
+      const Cx<T> v = nodal_restrict_acc<T>(NodesNear<T, LP, 0>(R, site, p));
+      set_planar<T, LP>(base + C.bo[l + 1], gc.nm, site.b * gc.n + site.a, v);
     }
     __syncthreads();
   }
-  dense_solve<T>(static_cast<const T*>(C.inv) + (int64_t)slot * C.nc * C.nc * 2, C.nc, lds_vec(base, C, false, last, 1),
-                 lds_vec(base, C, false, last, 0));
-  __syncthreads();
+  {
+    const Geo& g = C.L[last].g;
+    const P1 X(base + C.xo[last], g);
+    dense_solve<T>(inv, (int)C.nc, base + C.bo[last],
+                   base + C.ro, C.groups, [&](int i, Cx<T> v) {
+                     int j1, j2;
+                     split_index(i, g.n, j1, j2);
+                     X.store(0, X.index(j1, j2), v);
+                   });
+  }
+#pragma unroll 1
   for (int l = last - 1; l >= 0; --l) {
     const Geo& g = C.L[l].g;
-    const Geo& gc = C.L[l + 1].g;
-    T* x = lds_vec(base, C, false, l, 0);
-    const T* xc = lds_vec(base, C, false, l + 1, 0);
-    for (int64_t d = tid; d < g.nm; d += nt) {
-      const Cx<T> v = nodal_prolong_at<T>(xc, gc, g, d, p);
-      x[d] += v.re;
-      x[g.nm + d] += v.im;
+    const PL X(base + C.xo[l], g), Xc(base + C.xo[l + 1], C.L[l + 1].g);
+    if (l < last - 1) {
+      site.place<LP>(g);
+      load_rhs(base + C.bo[l], g);
+    }
+    if (site.on) {
+      const int a = site.a, b = site.b, a1 = site.xh ? 0 : a + 1, b1 = site.yh ? 0 : b + 1;
+      const Cx<T> c00 = Xc.load(0, Xc.index(a, b));
+      Cx<T> c10 = Xc.load(0, Xc.index(a1, b)), c01 = Xc.load(0, Xc.index(a, b1)), c11 = Xc.load(0, Xc.index(a1, b1));
+      if (site.xh) {
+        c10 = rotate<T, LP>(c10, p.ar, p.ai);
+        c11 = rotate<T, LP>(c11, p.ar, p.ai);
+      }
+      if (site.yh) {
+        c01 = rotate<T, LP>(c01, p.br, p.bi);
+        c11 = rotate<T, LP>(c11, p.br, p.bi);
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int i = site.row[(c >> 1) + 1] + site.col[(c & 1) + 1];
+        X.store(0, i, X.load(0, i) + nodal_prolong_combine<T>(c00, c10, c01, c11, c & 1, c >> 1));
+      }
     }
     __syncthreads();
-    const T* b = lds_vec(base, C, false, l, 1);
-    for (int it = 0; it < C.nu_post; ++it)
-      for (int c = 3; c >= 0; --c) {
-        nodal_colour<T>(g, x, b, c, C.ns, p);
-        __syncthreads();
-      }
+#pragma unroll 1
+    for (int it = 0; it < C.nu_post; ++it) nodal_sweep<T, LP, true>(X, rhs, C.ns, site, p);
   }
-  T* xg = colp(xv, sj, C.L[0].g.nm);
-  const T* x0 = lds_vec(base, C, false, 0, 0);
-  for (int64_t i = tid; i < 2 * C.L[0].g.nm; i += nt) xg[i] = x0[i];
+  const Geo& g = C.L[0].g;
+  T* xg = colp(xv, sj, g.nm);
+  const PL X(base + C.xo[0], g);
+  if (site.on)
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      set_planar<T, LP>(xg, g.nm, site.node(c), X.load(0, site.row[(c >> 1) + 1] + site.col[(c & 1) + 1]));
 }
 
 int g_lds_cap = -1;
@@ -255,8 +543,10 @@ int lds_cap() {
     int dev = 0, cap = 65536;
     (void)hipGetDevice(&dev);
     if (hipDeviceGetAttribute(&cap, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) cap = 65536;
-    const void* ks[] = {(const void*)k_edge_vcycle_fused<double>, (const void*)k_edge_vcycle_fused<float>,
-                        (const void*)k_nodal_vcycle_fused<double>, (const void*)k_nodal_vcycle_fused<float>};
+    const void* ks[] = {(const void*)k_edge_vcycle_fused<double, 1>,  (const void*)k_edge_vcycle_fused<double, 2>,
+                        (const void*)k_edge_vcycle_fused<float, 1>,   (const void*)k_edge_vcycle_fused<float, 2>,
+                        (const void*)k_nodal_vcycle_fused<double, 1>, (const void*)k_nodal_vcycle_fused<double, 2>,
+                        (const void*)k_nodal_vcycle_fused<float, 1>,  (const void*)k_nodal_vcycle_fused<float, 2>};
     for (const void* k : ks)
       if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, cap) != hipSuccess) cap = 65536;
     g_lds_cap = cap;
@@ -264,52 +554,68 @@ int lds_cap() {
   return g_lds_cap;
 }
 
+// LDS offsets of a cycle's vectors (elements); returns their total.  The residual lives only
+// between a level's smoothing and its restriction: one buffer, sized for the first level, which
+// also holds the dense solve's parts (for as many groups of 64 rows at a time as fit, at least one).
+int64_t fused_layout(CoarseCycle& C, bool edge) {
+  const int64_t comps = edge ? 4 : 2;
+  int64_t o = 0;
+  for (int l = 0; l < C.nlev; ++l) {
+    const Geo& g = C.L[l].g;
+    C.xo[l] = (int)o;
+    o += comps * (2 * ((g.n + 1) / 2)) * g.m;
+    C.bo[l] = (int)o;
+    o += comps * g.nm;
+  }
+  const int64_t parts = 64 * 2 * kDenseParts, r = comps * C.L[0].g.nm;
+  C.ro = (int)o;
+  C.groups = r >= parts ? (int)(r / parts) : 1;
+  return o + (r >= parts ? r : parts);
+}
+
 }  // namespace
 
 size_t fused_lds_bytes(const CoarseCycle& C, bool edge, size_t elem) {
-  size_t b = 0;
-  for (int l = 0; l < C.nlev; ++l) {
-    const int64_t len = 2 * (edge ? C.L[l].g.ne : C.L[l].g.nm);
-    b += (size_t)len * elem * (l + 1 < C.nlev ? 3 : 2);
-  }
-  return b;
+  CoarseCycle c = C;
+  return (size_t)fused_layout(c, edge) * elem;
 }
 
 size_t fused_lds_limit() { return (size_t)lds_cap(); }
 
 namespace {
-// Enough threads for one patch node (edge) or node (nodal) of a colour on the first fused
-// level each, between 256 and kFusedMaxThreads.  Results do not depend on it.
-int fused_threads(const CoarseCycle& C) {
-  static const int forced = [] {
-    const char* e = std::getenv("BL_FUSED_THREADS");
-    const int v = e ? std::atoi(e) : 0;
-    return v >= 64 && v <= kFusedMaxThreads && v % 64 == 0 ? v : 0;
-  }();
-  if (forced) return forced;
-  const int64_t per_colour = C.L[0].g.nm / 4;
-  int nt = 256;
-  while (nt < kFusedMaxThreads && nt < per_colour) nt *= 2;
-  return nt;
+// lanes * (coarse nodes below the first fused level) threads, in whole waves, and at least 256 for
+// the dense solve.
+int fused_threads(const CoarseCycle& C, int lanes) {
+  const int64_t t = lanes * (C.L[0].g.nm / 4);
+  return t <= 256 ? 256 : (int)((t + 63) / 64 * 64);
 }
 }  // namespace
 
+// Two lanes per coarse node where the workgroup has them (see the head of this file).
 template <typename T>
-void edge_vcycle_fused(View<const T> b, View<T> x, const CoarseCycle& C, const Phase* ph, const double* mu,
+void edge_vcycle_fused(View<const T> b, View<T> x, const CoarseCycle& cyc, const Phase* ph, const double* mu,
                        const Launch& L) {
   const int nb = L.nact * L.ncps;
   if (nb <= 0) return;
-  const size_t lds = fused_lds_bytes(C, true, sizeof(T));
+  CoarseCycle C = cyc;
+  const size_t lds = (size_t)fused_layout(C, true) * sizeof(T);
   (void)lds_cap();
-  k_edge_vcycle_fused<T><<<nb, fused_threads(C), lds, L.st>>>(b, x, C, ph, mu, L.slots, L.ncps);
+  if (fused_threads(C, 2) <= edge_threads<T, 2>())
+    k_edge_vcycle_fused<T, 2><<<nb, fused_threads(C, 2), lds, L.st>>>(b, x, C, ph, mu, L.slots, L.ncps);
+  else
+    k_edge_vcycle_fused<T, 1><<<nb, fused_threads(C, 1), lds, L.st>>>(b, x, C, ph, mu, L.slots, L.ncps);
 }
 template <typename T>
-void nodal_vcycle_fused(View<const T> b, View<T> x, const CoarseCycle& C, const Phase* ph, const Launch& L) {
+void nodal_vcycle_fused(View<const T> b, View<T> x, const CoarseCycle& cyc, const Phase* ph, const Launch& L) {
   const int nb = L.nact * L.ncps;
   if (nb <= 0) return;
-  const size_t lds = fused_lds_bytes(C, false, sizeof(T));
+  CoarseCycle C = cyc;
+  const size_t lds = (size_t)fused_layout(C, false) * sizeof(T);
   (void)lds_cap();
-  k_nodal_vcycle_fused<T><<<nb, fused_threads(C), lds, L.st>>>(b, x, C, ph, L.slots, L.ncps);
+  if (fused_threads(C, 2) <= nodal_threads<T, 2>())
+    k_nodal_vcycle_fused<T, 2><<<nb, fused_threads(C, 2), lds, L.st>>>(b, x, C, ph, L.slots, L.ncps);
+  else
+    k_nodal_vcycle_fused<T, 1><<<nb, fused_threads(C, 1), lds, L.st>>>(b, x, C, ph, L.slots, L.ncps);
 }
 template void edge_vcycle_fused<double>(View<const double>, View<double>, const CoarseCycle&, const Phase*, const double*, const Launch&);
 template void edge_vcycle_fused<float>(View<const float>, View<float>, const CoarseCycle&, const Phase*, const double*, const Launch&);

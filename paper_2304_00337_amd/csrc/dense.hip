@@ -4,7 +4,7 @@
 //    definite, no pivoting), and applied as a dense matrix-vector product;
 //  * tall-skinny Gram products X^* W of planar FP64 blocks (LDS-staged, register-tiled);
 //  * block recombination S Y.
-#include "internal.h"
+#include "stencil_common.h"
 
 #include <type_traits>
 
@@ -273,35 +273,32 @@ void invert_coarse(double* ke, float* ke32, int64_t ne, double* kn, float* kn32,
   k_invert_finish<<<dim3((unsigned)((big * big + 255) / 256), (unsigned)(2 * L.nact)), 256, 0, L.st>>>(me, mn, L.slots);
 }
 
-// x = Inv_s b for a Hermitian Inv_s (row-major interleaved); row i of Inv_s is read as the
-// conjugate of column i, so that consecutive threads read consecutive entries.
+// x = Inv_s b: 64 rows per workgroup, one per lane; each of the four waves sums two of a row's
+// parts (dense_part), which then combine in LDS.
 template <typename T>
-__global__ __launch_bounds__(256) void k_dense_apply(const T* __restrict__ inv, int64_t n, View<const T> bv,
-                                                     View<T> xv, const int* __restrict__ slots, int ncps) {
-  const int si = (int)blockIdx.y / ncps;
-  const int slot = slots ? slots[si] : si, col = (int)blockIdx.y % ncps;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  inv += (int64_t)slot * n * n * 2;
-  const T* bc = bv.p + ((int64_t)slot * bv.cps + bv.off + col) * 2 * n;
-  T sr = 0, si_ = 0;
-  // (unrolled: the loads of several terms are in flight; the summation order is unchanged)
-#pragma unroll 8
-  for (int64_t l = 0; l < n; ++l) {
-    const T ar = inv[2 * (l * n + i)], ai = -inv[2 * (l * n + i) + 1];
-    const T br = bc[l], bi = bc[n + l];
-    sr += ar * br - ai * bi;
-    si_ += ar * bi + ai * br;
-  }
-  T* xc = xv.p + ((int64_t)slot * xv.cps + xv.off + col) * 2 * n;
-  xc[i] = sr;
-  xc[n + i] = si_;
+__global__ __launch_bounds__(256) void k_dense_apply(const T* __restrict__ inv, int n, View<const T> bv, View<T> xv,
+                                                     const int* __restrict__ slots, int ncps) {
+  __shared__ T part[2 * kDenseParts][64];
+  const SJ sj = slot_col(slots, ncps);
+  const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int i = (int)blockIdx.x * 64 + lane;
+  inv += (int64_t)sj.slot * n * n * 2;
+  const T* bc = colp(bv, sj, n);
+  if (i < n)
+    for (int k = wave; k < kDenseParts; k += 4) {
+      const Cx<T> v = dense_part<T>(inv, n, bc, i, n * k / kDenseParts, n * (k + 1) / kDenseParts);
+      part[2 * k][lane] = v.re;
+      part[2 * k + 1][lane] = v.im;
+    }
+  __syncthreads();
+  if (wave < 2 && i < n)   // real, then imaginary parts
+    colp(xv, sj, n)[wave * n + i] = dense_sum([&](int k) { return part[2 * k + wave][lane]; });
 }
 template <typename T>
 void dense_apply(const void* inv, int64_t n, View<const T> b, View<T> x, const Launch& L) {
-  dim3 grid((unsigned)((n + 255) / 256), (unsigned)(L.nact * L.ncps));
+  dim3 grid((unsigned)((n + 63) / 64), (unsigned)(L.nact * L.ncps));
   if (grid.y == 0) return;
-  k_dense_apply<T><<<grid, 256, 0, L.st>>>(reinterpret_cast<const T*>(inv), n, b, x, L.slots, L.ncps);
+  k_dense_apply<T><<<grid, 256, 0, L.st>>>(reinterpret_cast<const T*>(inv), (int)n, b, x, L.slots, L.ncps);
 }
 template void dense_apply<double>(const void*, int64_t, View<const double>, View<double>, const Launch&);
 template void dense_apply<float>(const void*, int64_t, View<const float>, View<float>, const Launch&);

@@ -227,7 +227,7 @@ struct CoarseLevel {
   PatchT T4;
   const double* k64;    // kappa, slot-major (nm per slot)
   const float* k32;
-  const double* si64;   // patch inverses, slot-major (6 nm per slot); null on the coarsest
+  const double* si64;   // patch inverses, slot-major (kPatchW nm per slot); null on the coarsest
   const float* si32;
 };
 struct CoarseCycle {
@@ -235,6 +235,9 @@ struct CoarseCycle {
   int nu_pre, nu_post;
   int64_t nc;           // unknowns of the coarsest level (edges or nodes)
   const void* inv;      // its inverse in the cycle's precision, slot-major (nc x nc complex)
+  int xo[kMaxFused];    // LDS offsets (elements): iterate and right-hand side per level, and the
+  int bo[kMaxFused];    // residual; groups of 64 rows that the dense solve takes at a time (set by
+  int ro, groups;       // the launch)
   NodalStencil ns;      // nodal cycles
   CoarseLevel L[kMaxFused];
 };

@@ -306,7 +306,7 @@ CoarseCycle coarse_cycle(const bl_solver* s, int first, const void* inv, int64_t
 int plan_fusion(const bl_solver* s, bool edge, size_t elem) {
   if (!s->opts.coarse_fuse) return -1;
   const int nl = (int)s->lv.size();
-  const size_t cap = std::min<size_t>(fused_lds_limit(), 144 * 1024);
+  const size_t cap = fused_lds_limit();
   int best = -1;
   for (int f = nl - 2; f >= 0 && nl - f <= kMaxFused; --f) {
     if (s->lv[f].g.nm > 4096) break;

@@ -82,6 +82,67 @@ __device__ __forceinline__ T* colp(View<T> v, SJ s, int64_t N) {
   return v.p + ((int64_t)s.slot * v.cps + v.off + s.j) * 2 * N;
 }
 
+// The neighbouring lane's value (lane ^ 1).
+__device__ __forceinline__ float lane_xor1(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, false));
+}
+__device__ __forceinline__ double lane_xor1(double x) {
+  const long long b = __builtin_bit_cast(long long, x);
+  const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffLL), 0xB1, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0xB1, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Explicit fused multiply-adds (contraction is otherwise off), so that every kernel sharing
+// these bodies rounds the same way.
+template <typename T>
+__device__ __forceinline__ T fmat(T a, T b, T c);
+template <>
+__device__ __forceinline__ float fmat<float>(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+template <>
+__device__ __forceinline__ double fmat<double>(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// Part of row i of x = Inv b for a Hermitian n x n Inv (row i read as the conjugate of column i, so
+// that the lanes of a wave, one row each, read consecutive entries): terms l0 .. l1 - 1, in order,
+// the loads of 16 in flight.  l0 and l1 are the same for the whole wave.  A row is summed in
+// kDenseParts parts [n k / 8, n (k + 1) / 8), which dense_sum combines.
+constexpr int kDenseParts = 8;
+template <int U, typename T>
+__device__ __forceinline__ void dense_terms(const T* __restrict__ inv, int n, const T* b, int i, int l, int l1, Cx<T>& s) {
+  struct alignas(2 * sizeof(T)) Pair {
+    T r, i;
+  };
+  Pair a[U];
+  T br[U], bi[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {   // past the end: zeros times the last entry
+    const int k = l + u < l1 ? l + u : l1 - 1;
+    a[u] = reinterpret_cast<const Pair*>(inv + 2 * (int64_t)k * n)[i];
+    br[u] = l + u < l1 ? b[k] : (T)0;
+    bi[u] = l + u < l1 ? b[n + k] : (T)0;
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {   // s += conj(a) b
+    s.re = fmat<T>(a[u].i, bi[u], fmat<T>(a[u].r, br[u], s.re));
+    s.im = fmat<T>(-a[u].i, br[u], fmat<T>(a[u].r, bi[u], s.im));
+  }
+}
+template <typename T>
+__device__ __forceinline__ Cx<T> dense_part(const T* __restrict__ inv, int n, const T* b, int i, int l0, int l1) {
+  Cx<T> s = {0, 0};
+  int l = l0;
+#pragma unroll 1
+  for (; l + 16 <= l1; l += 16) dense_terms<16>(inv, n, b, i, l, l + 16, s);
+#pragma unroll 1
+  for (; l < l1; l += 8) dense_terms<8>(inv, n, b, i, l, l1, s);
+  return s;
+}
+// part(k): part k's value of a row
+template <typename F>
+__device__ __forceinline__ auto dense_sum(const F& part) {
+  return ((part(0) + part(1)) + (part(2) + part(3))) + ((part(4) + part(5)) + (part(6) + part(7)));
+}
+
 // Plane wave w_j = exp(i t1 j1) exp(i t2 j2) of a slot from its factor tables.
 __device__ __forceinline__ Cx<double> pw_value(const PWDefl& d, int slot, int n, int j1, int j2) {
   const double* t = d.tab + (int64_t)slot * d.tabstride;

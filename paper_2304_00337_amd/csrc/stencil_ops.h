@@ -128,14 +128,6 @@ __device__ __forceinline__ void edge_AM(const TI* xc, int64_t N, int n, int m, i
   }
 }
 
-// Explicit fused multiply-adds (contraction is otherwise off), so that every kernel sharing
-// these bodies rounds the same way.
-template <typename T>
-__device__ __forceinline__ T fmat(T a, T b, T c);
-template <>
-__device__ __forceinline__ float fmat<float>(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-template <>
-__device__ __forceinline__ double fmat<double>(double a, double b, double c) { return __builtin_fma(a, b, c); }
 template <typename T>
 __device__ __forceinline__ Cx<T> cfma(T w, Cx<T> r, Cx<T> acc) {
   return {fmat<T>(w, r.re, acc.re), fmat<T>(w, r.im, acc.im)};
