@@ -4,7 +4,7 @@
 // solve, prolongation and post-smoothing on every remaining level — runs in one workgroup
 // per column, with all levels' vectors in LDS and a barrier between dependent passes.  The
 // per-point bodies are those of the per-level kernels (stencil_ops.h) and the coarsest solve
-// is k_dense_apply's (dense_row), so a fused cycle reproduces the per-level one bit for bit.
+// is dense_apply's (dense_part, dense_row), so a fused cycle reproduces the per-level one bit for bit.
 //
 // What bounds it: a chain of some 40 short dependent passes, one workgroup per column, so the
 // latency of a pass is what counts.  Therefore
@@ -19,7 +19,8 @@
 //    half the instructions of each;
 //  * values are interleaved complex and the even and the odd columns of a row stand apart, so that
 //    the lanes of a colour read consecutive words;
-//  * in the dense solve a lane takes a row and a wave an eighth of its terms, 16 loads in flight.
+//  * in the dense solve a lane takes a row and a wave an eighth of its terms, 16 loads in flight
+//    (FP32 nodal cycles: see dense_in_parts).
 // From a 32 x 32 level down (FP64): 28 us for edges and 15 us for nodes, against 76 and 41 us
 // with every read wrapped and phased by itself, coefficients loaded per pass and one thread per row of
 // the dense solve.
@@ -489,13 +490,24 @@ __global__ __launch_bounds__((nodal_threads<T, LP>())) void k_nodal_vcycle_fused
   }
   {
     const Geo& g = C.L[last].g;
-    const P1 X(base + C.xo[last], g);
-    dense_solve<T>(inv, (int)C.nc, base + C.bo[last],
-                   base + C.ro, C.groups, [&](int i, Cx<T> v) {
-                     int j1, j2;
-                     split_index(i, g.n, j1, j2);
-                     X.store(0, X.index(j1, j2), v);
-                   });
+    const int nc = (int)C.nc;
+    int j1, j2;
+    if constexpr (dense_in_parts<T>(false)) {
+      const P1 X(base + C.xo[last], g);
+      dense_solve<T>(inv, nc, base + C.bo[last], base + C.ro, C.groups, [&](int i, Cx<T> v) {
+        split_index(i, g.n, j1, j2);
+        X.store(0, X.index(j1, j2), v);
+      });
+    } else {
+      const Plane<T, 2> X(base + C.xo[last], g);
+#pragma unroll 1
+      for (int i = tid >> 1; i < nc; i += nt >> 1) {
+        const T v = dense_row<T>(inv, nc, base + C.bo[last], i, tid & 1);
+        split_index(i, g.n, j1, j2);
+        X.store(0, X.index(j1, j2), Cx<T>{v, 0});
+      }
+      __syncthreads();
+    }
   }
 #pragma unroll 1
   for (int l = last - 1; l >= 0; --l) {

@@ -276,7 +276,7 @@ void invert_coarse(double* ke, float* ke32, int64_t ne, double* kn, float* kn32,
 // x = Inv_s b: 64 rows per workgroup, one per lane; each of the four waves sums two of a row's
 // parts (dense_part), which then combine in LDS.
 template <typename T>
-__global__ __launch_bounds__(256) void k_dense_apply(const T* __restrict__ inv, int n, View<const T> bv, View<T> xv,
+__global__ __launch_bounds__(256) void k_dense_apply_parts(const T* __restrict__ inv, int n, View<const T> bv, View<T> xv,
                                                      const int* __restrict__ slots, int ncps) {
   __shared__ T part[2 * kDenseParts][64];
   const SJ sj = slot_col(slots, ncps);
@@ -294,14 +294,27 @@ __global__ __launch_bounds__(256) void k_dense_apply(const T* __restrict__ inv, 
   if (wave < 2 && i < n)   // real, then imaginary parts
     colp(xv, sj, n)[wave * n + i] = dense_sum([&](int k) { return part[2 * k + wave][lane]; });
 }
+// The same with the terms one after the other, two lanes per row (real and imaginary part).
 template <typename T>
-void dense_apply(const void* inv, int64_t n, View<const T> b, View<T> x, const Launch& L) {
-  dim3 grid((unsigned)((n + 63) / 64), (unsigned)(L.nact * L.ncps));
-  if (grid.y == 0) return;
-  k_dense_apply<T><<<grid, 256, 0, L.st>>>(reinterpret_cast<const T*>(inv), (int)n, b, x, L.slots, L.ncps);
+__global__ __launch_bounds__(256) void k_dense_apply(const T* __restrict__ inv, int n, View<const T> bv, View<T> xv,
+                                                     const int* __restrict__ slots, int ncps) {
+  const SJ sj = slot_col(slots, ncps);
+  const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x), i = t >> 1, part = t & 1;
+  if (i >= n) return;
+  const T* bc = colp(bv, sj, n);
+  colp(xv, sj, n)[part * n + i] = dense_row<T>(inv + (int64_t)sj.slot * n * n * 2, n, bc, i, part);
 }
-template void dense_apply<double>(const void*, int64_t, View<const double>, View<double>, const Launch&);
-template void dense_apply<float>(const void*, int64_t, View<const float>, View<float>, const Launch&);
+template <typename T>
+void dense_apply(const void* inv, int64_t n, bool edge, View<const T> b, View<T> x, const Launch& L) {
+  const bool parts = dense_in_parts<T>(edge);
+  dim3 grid((unsigned)(parts ? (n + 63) / 64 : (2 * n + 255) / 256), (unsigned)(L.nact * L.ncps));
+  if (grid.y == 0) return;
+  const T* m = reinterpret_cast<const T*>(inv);
+  if (parts) k_dense_apply_parts<T><<<grid, 256, 0, L.st>>>(m, (int)n, b, x, L.slots, L.ncps);
+  else k_dense_apply<T><<<grid, 256, 0, L.st>>>(m, (int)n, b, x, L.slots, L.ncps);
+}
+template void dense_apply<double>(const void*, int64_t, bool, View<const double>, View<double>, const Launch&);
+template void dense_apply<float>(const void*, int64_t, bool, View<const float>, View<float>, const Launch&);
 
 // ------------------------------------------------------------------------------------------
 // Gram products.  Block (16 x 16 threads) computes a 64 x 64 tile of X^* W over a range of

@@ -263,7 +263,7 @@ void invert_coarse(double* ke, float* ke32, int64_t ne, double* kn, float* kn32,
 size_t invert_panel_doubles(int64_t ne, int64_t nn);
 // x = Inv_s b per column, Inv_s = inv + s * n * n (complex, Hermitian)
 template <typename T>
-void dense_apply(const void* inv, int64_t n, View<const T> b, View<T> x, const Launch& L);
+void dense_apply(const void* inv, int64_t n, bool edge, View<const T> b, View<T> x, const Launch& L);
 
 // Per slot: G_s (q x r, row-major interleaved complex, at out + s * q * r * 2) = X_s^* W_s of
 // planar FP64 column views of length len.  Returns -1 (nothing launched) when partial_cap

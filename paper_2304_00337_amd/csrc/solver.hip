@@ -324,7 +324,7 @@ void vcycle_edge(bl_solver* s, int l, View<const T> b, View<T> x, const Launch& 
   Level& lv = s->lv[l];
   const int nl = (int)s->lv.size();
   if (l == nl - 1) {
-    dense_apply<T>(kc_inv<T>(s), s->nce, b, x, L);
+    dense_apply<T>(kc_inv<T>(s), s->nce, true, b, x, L);
     s->launches += 1;
     return;
   }
@@ -446,7 +446,7 @@ bool vcycle_nodal(bl_solver* s, int l, View<const T> b, View<T> x, const Launch&
   Level& lv = s->lv[l];
   const int nl = (int)s->lv.size();
   if (l == nl - 1) {
-    dense_apply<T>(pc_inv<T>(s), s->ncn, b, x, L);
+    dense_apply<T>(pc_inv<T>(s), s->ncn, false, b, x, L);
     s->launches += 1;
     return false;
   }
@@ -1590,11 +1590,11 @@ int apply_t(bl_solver* s, int op, int level, int ncols, const void* xv, const vo
     }
     case BL_OP_COARSE_EDGE:
       if (level != nl - 1) return set_error(BL_EINVAL, "coarse solve only on the coarsest level%s");
-      dense_apply<T>(kc_inv<T>(s), s->nce, x, out, La);
+      dense_apply<T>(kc_inv<T>(s), s->nce, true, x, out, La);
       break;
     case BL_OP_COARSE_NODAL:
       if (level != nl - 1) return set_error(BL_EINVAL, "coarse solve only on the coarsest level%s");
-      dense_apply<T>(pc_inv<T>(s), s->ncn, x, out, La);
+      dense_apply<T>(pc_inv<T>(s), s->ncn, false, x, out, La);
       break;
     case BL_OP_EIGRES:
       if (!yv) return set_error(BL_EINVAL, "eigenvalues (y) missing%s");

@@ -6,6 +6,8 @@
 
 #include "internal.h"
 
+#include <type_traits>
+
 // No contraction into FMAs in these helpers either: they are inlined into the per-level
 // kernels and the fused coarse cycles alike, which must round identically.
 #pragma clang fp contract(off)
@@ -141,6 +143,45 @@ __device__ __forceinline__ Cx<T> dense_part(const T* __restrict__ inv, int n, co
 template <typename F>
 __device__ __forceinline__ auto dense_sum(const F& part) {
   return ((part(0) + part(1)) + (part(2) + part(3))) + ((part(4) + part(5)) + (part(6) + part(7)));
+}
+
+// Whether the coarsest solves sum their rows in parts.  FP32 nodal cycles do not: the projection puts
+// their results into FP64 vectors, which another order of the terms would move by FP32 roundings (the
+// edge cycles only precondition).  Their matrices are the smallest ones.
+template <typename T>
+constexpr bool dense_in_parts(bool edge) { return edge || sizeof(T) == 8; }
+
+// Row i of the same product, its real (part = 0) or imaginary part, the terms one after the other,
+// the loads of 32 in flight.
+template <int U, typename T>
+__device__ __forceinline__ void dense_run(const T* __restrict__ inv, int n, const T* bu, const T* bv, int i, bool im,
+                                          int l, T& s) {
+  struct alignas(2 * sizeof(T)) Pair {
+    T r, i;
+  };
+  Pair a[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {   // past the end: read again, not added
+    const int k = l + u < n ? l + u : n - 1;
+    a[u] = reinterpret_cast<const Pair*>(inv + 2 * (int64_t)k * n)[i];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {   // conj(a) b: ar br + ai bi, or ar bi - ai br
+    const int k = l + u < n ? l + u : n - 1;
+    const T t = a[u].r * bu[k] + (im ? -a[u].i : a[u].i) * bv[k];
+    s = l + u < n ? s + t : s;
+  }
+}
+template <typename T>
+__device__ __forceinline__ T dense_row(const T* __restrict__ inv, int n, const T* b, int i, int part) {
+  const T *bu = b + part * n, *bv = b + (1 - part) * n;
+  T s = 0;
+  int l = 0;
+#pragma unroll 1
+  for (; l + 32 <= n; l += 32) dense_run<32>(inv, n, bu, bv, i, part != 0, l, s);
+#pragma unroll 1
+  for (; l < n; l += 8) dense_run<8>(inv, n, bu, bv, i, part != 0, l, s);
+  return s;
 }
 
 // Plane wave w_j = exp(i t1 j1) exp(i t2 j2) of a slot from its factor tables.
