@@ -142,7 +142,7 @@ struct SweepFuse {
 
 // One whole smoothing sweep (four colours; reverse colour order when backward) as one launch
 // over LDS tiles with halos, bit-identical to the four colour launches; `tile` selects the
-// tile shape (0: 32 x 32, 1: 64 x 32 nodes; FP64 edge sweeps 32 x 32).  Reads the iterate
+// edge sweeps' tile shape (0: 32 x 32, 1: 64 x 32 nodes; FP64 32 x 32).  Reads the iterate
 // from xin and writes it to xout, which must be different buffers; zero_start: the iterate is
 // zero on entry (xin is then not read).  sweep.hip.
 template <typename T>
@@ -155,7 +155,7 @@ void edge_sweep(View<const T> xin, View<T> xout, View<const T> b, const double* 
 bool edge_sweep_restricts(size_t elem);
 template <typename T>
 void nodal_sweep(View<const T> xin, View<T> xout, View<const T> b, const Geo& g, const Phase* ph,
-                 const NodalStencil& c, bool backward, bool zero_start, int tile, const Launch& L,
+                 const NodalStencil& c, bool backward, bool zero_start, const Launch& L,
                  const SweepFuse<T>& fz = SweepFuse<T>{});
 void patch_setup(const double* kappa, const Geo& g, const double* q, const PatchT& T4, const double* mu,
                  double* sinv64, float* sinv32, int nslots, hipStream_t st);

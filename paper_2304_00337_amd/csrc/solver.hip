@@ -358,7 +358,7 @@ void vcycle_edge(bl_solver* s, int l, View<const T> b, View<T> x, const Launch& 
       }
       timing_begin(s, l);
       edge_sweep<T>(cv(prev), dst, b, lv.kappa64, lv.kappa32, lv.sinv64, lv.sinv32, lv.g, s->ph_d, s->mu_d, lv.T4,
-                    false, it == 0, s->tune_sweep[0], L, fz);
+                    false, it == 0, s->tune_sweep, L, fz);
       timing_end(s, l, ncols, smooth_bytes(lv.g, sizeof(T), true, it == 0, ncols, L.nact, fz.bc.p ? 0.25 : 0.0));
       prev = dst;
     }
@@ -372,7 +372,7 @@ void vcycle_edge(bl_solver* s, int l, View<const T> b, View<T> x, const Launch& 
       }
       timing_begin(s, l);
       edge_sweep<T>(cv(prev), dst, b, lv.kappa64, lv.kappa32, lv.sinv64, lv.sinv32, lv.g, s->ph_d, s->mu_d, lv.T4,
-                    true, false, s->tune_sweep[0], L, fz);
+                    true, false, s->tune_sweep, L, fz);
       timing_end(s, l, ncols, smooth_bytes(lv.g, sizeof(T), true, false, ncols, L.nact, it == 0 ? 0.25 : 0.0));
       prev = dst;
     }
@@ -390,7 +390,7 @@ void vcycle_edge(bl_solver* s, int l, View<const T> b, View<T> x, const Launch& 
       View<T> dst = ((npre - 1 - it) % 2 == 0) ? x : r;
       timing_begin(s, l);
       edge_sweep<T>(cv(src), dst, b, lv.kappa64, lv.kappa32, lv.sinv64, lv.sinv32, lv.g, s->ph_d, s->mu_d, lv.T4,
-                    false, it == 0, s->tune_sweep[0], L);
+                    false, it == 0, s->tune_sweep, L);
       timing_end(s, l, ncols, smooth_bytes(lv.g, sizeof(T), true, it == 0, ncols, L.nact));
       nl_launch += 1;
       continue;
@@ -415,7 +415,7 @@ void vcycle_edge(bl_solver* s, int l, View<const T> b, View<T> x, const Launch& 
       View<T> dst = (cur.p == x.p && cur.off == x.off && cur.cps == x.cps) ? r : x;
       timing_begin(s, l);
       edge_sweep<T>(cv(cur), dst, b, lv.kappa64, lv.kappa32, lv.sinv64, lv.sinv32, lv.g, s->ph_d, s->mu_d, lv.T4,
-                    true, false, s->tune_sweep[0], L);
+                    true, false, s->tune_sweep, L);
       timing_end(s, l, ncols, smooth_bytes(lv.g, sizeof(T), true, false, ncols, L.nact));
       cur = dst;
       nl_launch += 1;
@@ -476,7 +476,7 @@ bool vcycle_nodal(bl_solver* s, int l, View<const T> b, View<T> x, const Launch&
         fz.bc = bc;
         fz.gc = C.g;
       }
-      nodal_sweep<T>(cv(prev), dst, b, lv.g, s->ph_d, s->ns, false, it == 0, s->tune_sweep[1], L, fz);
+      nodal_sweep<T>(cv(prev), dst, b, lv.g, s->ph_d, s->ns, false, it == 0, L, fz);
       prev = dst;
     }
     vcycle_nodal<T>(s, l + 1, cv(bc), xc, L);
@@ -495,7 +495,7 @@ bool vcycle_nodal(bl_solver* s, int l, View<const T> b, View<T> x, const Launch&
         fz.res = *res_out;
         if (res_done) *res_done = true;
       }
-      nodal_sweep<T>(cv(prev), dst, b, lv.g, s->ph_d, s->ns, true, false, s->tune_sweep[1], L, fz);
+      nodal_sweep<T>(cv(prev), dst, b, lv.g, s->ph_d, s->ns, true, false, L, fz);
       prev = dst;
     }
     s->launches += npre + npost;
@@ -510,7 +510,7 @@ bool vcycle_nodal(bl_solver* s, int l, View<const T> b, View<T> x, const Launch&
     if (tiled) {
       View<T> src = ((npre - it) % 2 == 0) ? x : r;
       View<T> dst = ((npre - 1 - it) % 2 == 0) ? x : r;
-      nodal_sweep<T>(cv(src), dst, b, lv.g, s->ph_d, s->ns, false, it == 0, s->tune_sweep[1], L);
+      nodal_sweep<T>(cv(src), dst, b, lv.g, s->ph_d, s->ns, false, it == 0, L);
       nl_launch += 1;
     } else {
       for (int c = 0; c < 4; ++c) nodal_gs<T>(x, b, lv.g, s->ph_d, s->ns, c, s->tune_nodal, L);
@@ -528,7 +528,7 @@ bool vcycle_nodal(bl_solver* s, int l, View<const T> b, View<T> x, const Launch&
     nodal_prolong_to<T>(cv(xc), C.g, cv(x), cur, lv.g, s->ph_d, L);
     for (int it = 0; it < npost; ++it) {
       View<T> dst = (cur.p == x.p && cur.off == x.off && cur.cps == x.cps) ? r : x;
-      nodal_sweep<T>(cv(cur), dst, b, lv.g, s->ph_d, s->ns, true, false, s->tune_sweep[1], L);
+      nodal_sweep<T>(cv(cur), dst, b, lv.g, s->ph_d, s->ns, true, false, L);
       cur = dst;
       nl_launch += 1;
     }
@@ -1612,9 +1612,9 @@ int apply_t(bl_solver* s, int op, int level, int ncols, const void* xv, const vo
       const bool back = op == BL_OP_EDGE_SWEEP_BACK || op == BL_OP_NODAL_SWEEP_BACK;
       if (op == BL_OP_EDGE_SWEEP || op == BL_OP_EDGE_SWEEP_BACK)
         edge_sweep<T>(x, out, y, L.kappa64, L.kappa32, L.sinv64, L.sinv32, L.g, s->ph_d, s->mu_d, L.T4, back, false,
-                      s->tune_sweep[0], La);
+                      s->tune_sweep, La);
       else
-        nodal_sweep<T>(x, out, y, L.g, s->ph_d, s->ns, back, false, s->tune_sweep[1], La);
+        nodal_sweep<T>(x, out, y, L.g, s->ph_d, s->ns, back, false, La);
       break;
     }
     default: return set_error(BL_EINVAL, "unknown operator%s");

@@ -227,6 +227,14 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
   return x * q + (x < r ? x : r) + i;
 }
 
+// The value `off` bytes (below 4 GB) past a base that is uniform in the wave: the base stays in scalar
+// registers and the lane's part of the address is 32 bits.
+template <typename T>
+__device__ __forceinline__ T& at32(T* base, unsigned off) {
+  using C = typename std::conditional<std::is_const<T>::value, const char, char>::type;
+  return *reinterpret_cast<T*>(reinterpret_cast<C*>(base) + off);
+}
+
 template <typename T>
 __device__ __forceinline__ T kap(const double* k64, const float* k32, int64_t i);
 template <>

@@ -51,6 +51,9 @@ constexpr int kRestrict = 1, kProlong = 2, kBase = 4;
 // the tile's nodes (as the residual kernel computes it), for which the iterate must be exact
 // one node around the tile.
 constexpr int kResid = 8;
+// kZero (nodal forward sweeps): the iterate is zero on entry, not read and not stored before a node's
+// own pass, which leaves out the neighbours that no pass has reached.
+constexpr int kZero = 16;
 constexpr int kLoR = 6;
 constexpr int kHiER = 6;
 
@@ -145,21 +148,6 @@ struct TileRhs {
     if (CY && d2 != 0) j2 = sm.cross_y(d2) ? (d2 < 0 ? m - 1 : 0) : j2;
     const int64_t k = (c ? nm : 0) + (int64_t)j2 * n + j1;
     return phased<CX, CY, T>(Cx<T>{bc[k], bc[N + k]}, d1, d2, sm, p);
-  }
-};
-
-// Nodal values around the node at box position (2i + PX, 2j + PY), two LDS planes.
-template <typename T, int BX, int BY, int PX, int PY, bool CX, bool CY>
-struct TileNodes {
-  using S = Split<BX, BY>;
-  const T* pl;
-  int i, j;
-  Seam<CX, CY> sm;
-  Ph<T> p;
-  __device__ __forceinline__ Cx<T> get(int d1, int d2) const {
-    const int sx = (PX + d1) & 1, sy = (PY + d2) & 1;
-    const T* q = pl + (sx + 2 * sy) * S::SUB + (j + ((PY + d2) >> 1)) * S::HX + i + ((PX + d1) >> 1);
-    return phased<CX, CY, T>(Cx<T>{q[0], q[S::N]}, d1, d2, sm, p);
   }
 };
 
@@ -513,295 +501,253 @@ __global__ __launch_bounds__(kMaxThreads) void k_edge_sweep(View<const T> xin, V
   }
 }
 
-// One colour pass of the nodal point Gauss-Seidel on the box.
-template <typename T, int BX, int BY, int COLOUR, bool CX, bool CY, int X0, int X1, int Y0, int Y1>
-__device__ __forceinline__ void nodal_pass(T* pl, const T* bc, const NodalStencil& st, int ox, int oy, int n, int m,
-                                           int64_t N, const Ph<T>& p) {
-  using S = Split<BX, BY>;
-  constexpr int PX = COLOUR & 1, PY = COLOUR >> 1;
-  static_assert((X0 & 1) == PX && (Y0 & 1) == PY && X0 >= 1 && Y0 >= 1 && X1 <= BX - 2 && Y1 <= BY - 2, "pass rectangle");
-  constexpr int B0X = X0, B0Y = Y0;
-  constexpr int CNX = (X1 - X0) / 2 + 1, CNY = (Y1 - Y0) / 2 + 1;
-  const T inv = (T)1 / (T)st.c0;
-  for (int t = threadIdx.x; t < CNX * CNY; t += nthreads()) {
-    const int i = (B0X >> 1) + t % CNX, j = (B0Y >> 1) + t / CNX;
-    const int bx = 2 * i + PX, by = 2 * j + PY;
-    const int p1 = CX ? wrapm(ox + bx, n) : ox + bx;
-    const int p2 = CY ? wrapm(oy + by, m) : oy + by;
-    const int64_t k = (int64_t)p2 * n + p1;
-    const TileNodes<T, BX, BY, PX, PY, CX, CY> X{pl, i, j, Seam<CX, CY>(p1, p2, n, m), p};
-    const Cx<T> r = Cx<T>{bc[k], bc[N + k]} - nodal_stencil_at<T>(X, st);
-    T* q = pl + (PX + 2 * PY) * S::SUB + j * S::HX + i;
-    q[0] += inv * r.re;
-    q[S::N] += inv * r.im;
-  }
-}
+// ---- nodal sweeps ---------------------------------------------------------------------------
+// A thread owns one 2 x 2 block of the box's nodes (blocks of HX a row, so that block t is entry t of
+// every parity sub-grid) in all passes: its addresses, its seam flags and its right-hand side are
+// worked out and loaded once, with the iterate, and a pass is LDS reads at constant offsets and
+// arithmetic.  Passes that dealt out a colour's nodes anew each time were bound by the vector units:
+// 230 to 330 instructions per node, three quarters of them addressing and reloading; this form takes
+// 160 to 240.  A sweep from zero (84 % of the vector issue) leaves out what is still zero; the
+// prolongating ones wait for memory half the time.  1024 x 1024 FP32, 48 columns, finest level:
+// restricting sweep 295 us, prolongating with residual 484, prolongating onto the base 416, against
+// 395, 624 and 486; 256 x 256 FP64: 73 and 48 us for the last two, against 103 and 84.
+constexpr int kNodalTile = 32, kNodalThreads = 512;
 
-template <typename T, int BX, int BY, bool BWD, bool CX, bool CY, int LO, int TX, int TY, int EA, int EB>
-__device__ __forceinline__ void nodal_passes(T* pl, const T* bc, const NodalStencil& st, int ox, int oy, int n, int m,
-                                             int64_t N, const Ph<T>& p) {
-  constexpr SweepRects R = sweep_rects(false, BX, BY, LO, TX, TY, EA, EB, BWD);
-  static_assert(R.ok, "the halo does not cover the sweep's dependency cone");
-#define BL_NPASS(k, c)                                                                                             \
-  nodal_pass<T, BX, BY, c, CX, CY, R.r[k].x0, R.r[k].x1, R.r[k].y0, R.r[k].y1>(pl, bc, st, ox, oy, n, m, N, p); \
-  __syncthreads();
-  BL_NPASS(0, BWD ? 3 : 0)
-  BL_NPASS(1, BWD ? 2 : 1)
-  BL_NPASS(2, BWD ? 1 : 2)
-  BL_NPASS(3, BWD ? 0 : 3)
-#undef BL_NPASS
-}
-
-// Residual b - P x on the box positions of parity (PX, PY) inside the residual window
-// [LO - 1, LO + TX - 1] x [LO - 1, LO + TY - 1] (the fine nodes that the restriction to the
-// tile's coarse nodes reads), as the residual kernel computes it, into rl (row-major window,
-// re plane then im plane).
-template <typename T, int BX, int BY, int PX, int PY, bool CX, bool CY, int LO, int TX, int TY>
-__device__ __forceinline__ void nodal_resid_pass(const T* pl, T* rl, const T* bc, const NodalStencil& st, int ox,
-                                                 int oy, int n, int m, int64_t N, const Ph<T>& p) {
-  constexpr int R0 = LO - 1, RW = TX + 1, RH = TY + 1;
-  constexpr int I0 = (R0 - PX + 1) / 2, I1 = (LO + TX - 1 - PX) / 2;
-  constexpr int J0 = (R0 - PY + 1) / 2, J1 = (LO + TY - 1 - PY) / 2;
-  constexpr int CNX = I1 - I0 + 1, CNY = J1 - J0 + 1;
-  for (int t = threadIdx.x; t < CNX * CNY; t += nthreads()) {
-    const int i = I0 + t % CNX, j = J0 + t / CNX;
-    const int bx = 2 * i + PX, by = 2 * j + PY;
-    const int p1 = CX ? wrapm(ox + bx, n) : ox + bx;
-    const int p2 = CY ? wrapm(oy + by, m) : oy + by;
-    const int64_t k = (int64_t)p2 * n + p1;
-    const TileNodes<T, BX, BY, PX, PY, CX, CY> X{pl, i, j, Seam<CX, CY>(p1, p2, n, m), p};
-    const Cx<T> r = Cx<T>{bc[k], bc[N + k]} - nodal_stencil_at<T>(X, st);
-    const int q = (by - R0) * RW + (bx - R0);
-    rl[q] = r.re;
-    rl[RW * RH + q] = r.im;
-  }
-}
-
-// Residual b - P x at the tile's nodes (box positions LO .. LO + TX - 1, LO .. LO + TY - 1),
-// straight to memory, as the residual kernel computes it.
-template <typename T, int BX, int BY, int PAR, bool CX, bool CY, int LO, int TX, int TY>
-__device__ __forceinline__ void nodal_tile_resid_par(const T* pl, const T* bc, T* ro, const NodalStencil& st, int ox,
-                                                     int oy, int n, int m, int64_t N, const Ph<T>& p) {
-  constexpr int PX = PAR & 1, PY = PAR >> 1;
-  constexpr int I0 = (LO - PX + 1) / 2, I1 = (LO + TX - 1 - PX) / 2;
-  constexpr int J0 = (LO - PY + 1) / 2, J1 = (LO + TY - 1 - PY) / 2;
-  constexpr int CNX = I1 - I0 + 1, CNY = J1 - J0 + 1;
-  for (int t = threadIdx.x; t < CNX * CNY; t += nthreads()) {
-    const int i = I0 + t % CNX, j = J0 + t / CNX;
-    const int bx = 2 * i + PX, by = 2 * j + PY;
-    const int p1 = CX ? wrapm(ox + bx, n) : ox + bx;
-    const int p2 = CY ? wrapm(oy + by, m) : oy + by;
-    if (ox + bx >= n || oy + by >= m) continue;   // past the grid's last tile column / row
-    const int64_t k = (int64_t)p2 * n + p1;
-    const TileNodes<T, BX, BY, PX, PY, CX, CY> X{pl, i, j, Seam<CX, CY>(p1, p2, n, m), p};
-    const Cx<T> r = Cx<T>{bc[k], bc[N + k]} - nodal_stencil_at<T>(X, st);
-    ro[k] = r.re;
-    ro[N + k] = r.im;
-  }
-}
-template <typename T, int BX, int BY, bool CX, bool CY, int LO, int TX, int TY>
-__device__ __forceinline__ void nodal_tile_resid(const T* pl, const T* bc, T* ro, const NodalStencil& st, int ox,
-                                                 int oy, int n, int m, int64_t N, const Ph<T>& p) {
-  nodal_tile_resid_par<T, BX, BY, 0, CX, CY, LO, TX, TY>(pl, bc, ro, st, ox, oy, n, m, N, p);
-  nodal_tile_resid_par<T, BX, BY, 1, CX, CY, LO, TX, TY>(pl, bc, ro, st, ox, oy, n, m, N, p);
-  nodal_tile_resid_par<T, BX, BY, 2, CX, CY, LO, TX, TY>(pl, bc, ro, st, ox, oy, n, m, N, p);
-  nodal_tile_resid_par<T, BX, BY, 3, CX, CY, LO, TX, TY>(pl, bc, ro, st, ox, oy, n, m, N, p);
-}
-
-// Residual window values around window position (x, y) (as fetch()).
-template <typename T, int RW, int RH, bool CX, bool CY>
-struct WindowNodes {
-  const T* rl;
-  int x, y;
+// The values around a node of block t in the iterate's planes; colours from FIRST on are still zero.
+template <typename T, typename S, int PX, int PY, bool CX, bool CY, int FIRST = 4>
+struct BlockNodes {
+  const T* pl;   // at entry t
   Seam<CX, CY> sm;
-  Ph<T> p;
+  const Ph<T>& p;
   __device__ __forceinline__ Cx<T> get(int d1, int d2) const {
-    const int q = (y + d2) * RW + x + d1;
-    return phased<CX, CY, T>(Cx<T>{rl[q], rl[RW * RH + q]}, d1, d2, sm, p);
+    const int sx = (PX + d1) & 1, sy = (PY + d2) & 1;
+    if (sx + 2 * sy >= FIRST) return {0, 0};
+    const T* q = pl + (sx + 2 * sy) * S::SUB + ((PY + d2) >> 1) * S::HX + ((PX + d1) >> 1);
+    return phased<CX, CY, T>(Cx<T>{q[0], q[S::N]}, d1, d2, sm, p);
   }
 };
 
-// Residual of the swept tile and its restriction to the tile's coarse nodes.
-template <typename T, int BX, int BY, bool CX, bool CY, int LO, int TX, int TY>
-__device__ __forceinline__ void nodal_restrict_tile(const T* pl, T* rl, const T* bc, T* bco, const NodalStencil& st,
-                                                    int ox, int oy, int t0x, int t0y, int n, int m, int64_t N,
-                                                    const Geo& gc, const Ph<T>& p) {
-  nodal_resid_pass<T, BX, BY, 0, 0, CX, CY, LO, TX, TY>(pl, rl, bc, st, ox, oy, n, m, N, p);
-  nodal_resid_pass<T, BX, BY, 1, 0, CX, CY, LO, TX, TY>(pl, rl, bc, st, ox, oy, n, m, N, p);
-  nodal_resid_pass<T, BX, BY, 0, 1, CX, CY, LO, TX, TY>(pl, rl, bc, st, ox, oy, n, m, N, p);
-  nodal_resid_pass<T, BX, BY, 1, 1, CX, CY, LO, TX, TY>(pl, rl, bc, st, ox, oy, n, m, N, p);
-  __syncthreads();
-  constexpr int HX = TX / 2, HY = TY / 2;
-  for (int t = threadIdx.x; t < HX * HY; t += nthreads()) {
-    const int jx = t % HX, jy = t / HX;
-    const int f1 = t0x + 2 * jx, f2 = t0y + 2 * jy;
-    if (f1 >= n || f2 >= m) continue;
-    const WindowNodes<T, TX + 1, TY + 1, CX, CY> R{rl, 2 * jx + 1, 2 * jy + 1, Seam<CX, CY>(f1, f2, n, m), p};
-    const Cx<T> v = nodal_restrict_acc<T>(R);
-    const int64_t J = (int64_t)(f2 >> 1) * gc.n + (f1 >> 1);
-    bco[J] = v.re;
-    bco[gc.nm + J] = v.im;
+template <typename T, bool BWD, int MODE>
+struct NodalShape {
+  static constexpr bool RES = (MODE & kRestrict) != 0, PRO = (MODE & kProlong) != 0, BAS = (MODE & kBase) != 0;
+  static constexpr bool TRES = (MODE & kResid) != 0, ZERO = (MODE & kZero) != 0;
+  static constexpr int TX = kNodalTile, LO = RES ? kLoR : kLo;
+  static constexpr int HI = TRES ? kHiN + 1 : kHiN;   // (the tile residual: exact one node above / right too)
+  static constexpr int BX = TX + LO + HI;
+  using S = Split<BX, BX>;
+  // coarse nodes under the box: fine box position b lies over coarse box position b >> 1 and its
+  // neighbours one up
+  static constexpr int CBX = (BX - 1) / 2 + 2, CB = CBX * CBX;
+  // exact margin the residual window (restriction) or the tile residual needs
+  static constexpr int EA = RES ? 2 : (TRES ? 1 : 0), EB = (RES || TRES) ? 1 : 0;
+  static constexpr SweepRects R = sweep_rects(false, BX, BX, LO, TX, TX, EA, EB, BWD);
+  static_assert(R.ok, "the halo does not cover the sweep's dependency cone");
+  static_assert(S::SUB <= kNodalThreads && CB <= kNodalThreads, "a block per thread");
+};
+
+// The values of a block's four nodes in a column, colour by colour: off is the byte offset of its
+// first node in a plane, row that of a row; wide: two neighbouring values in one load.
+template <typename T>
+__device__ __forceinline__ void load_block(const T* c, int64_t N, unsigned off, unsigned row, bool wide, Cx<T> (&v)[4]) {
+  struct alignas(2 * sizeof(T)) Pair {
+    T a, b;
+  };
+  if (wide) {
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      const Pair re = at32(reinterpret_cast<const Pair*>(c), off + y * row);
+      const Pair im = at32(reinterpret_cast<const Pair*>(c + N), off + y * row);
+      v[2 * y] = {re.a, im.a};
+      v[2 * y + 1] = {re.b, im.b};
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const unsigned o = off + (k >> 1) * row + (k & 1) * (unsigned)sizeof(T);
+      v[k] = {at32(c, o), at32(c + N, o)};
+    }
   }
 }
 
-template <typename T, int TX, int TY, bool BWD, int MODE>
-__global__ __launch_bounds__(kMaxThreads) void k_nodal_sweep(View<const T> xin, View<T> xout, View<const T> bv, Geo g,
-                                                          const Phase* __restrict__ phs, NodalStencil st,
-                                                          int zero_start, const int* __restrict__ slots, int ncps,
-                                                          int tiles_x, SweepFuse<T> fz) {
+template <typename T, bool BWD, int MODE, bool CX, bool CY>
+__device__ __forceinline__ void nodal_tile(T* pl, T* cl, const T* xc, T* xo, const T* bc, const T* cc, T* bco, const T* bs,
+                                           T* ro, const NodalStencil& st, int t0x, int t0y, int n, int m, int64_t N,
+                                           const Geo& gc, const Ph<T>& p, bool wide) {
+  using H = NodalShape<T, BWD, MODE>;
+  using S = typename H::S;
+  constexpr int LO = H::LO, BX = H::BX, TX = H::TX;
+  constexpr SweepRects R = H::R;
+  const int tid = (int)threadIdx.x;
+  const bool live = tid < S::SUB;
+  const int t = live ? tid : 0, a = t % S::HX, b = t / S::HX;
+  const int ox = t0x - LO, oy = t0y - LO;   // canonical node of box position 0 (unwrapped)
+  // canonical first node of the block (n, m, ox and oy are even: a block never straddles the seam,
+  // and where the box has an odd number of nodes its last block still lies in the grid)
+  const int p1 = CX ? wrapm(ox + 2 * a, n) : ox + 2 * a, p2 = CY ? wrapm(oy + 2 * b, m) : oy + 2 * b;
+  const unsigned off = (unsigned)(p2 * n + p1) * (unsigned)sizeof(T), row = (unsigned)n * (unsigned)sizeof(T);
+  Cx<T> rhs[4], u[4];
+  load_block(bc, N, off, row, wide, rhs);
+  if constexpr (!H::ZERO) load_block(xc, N, off, row, wide, u);
+  // the tile, whole rows at a time
+  constexpr int ROWS = kNodalThreads / TX, RK = TX / ROWS;
+  const int ix = tid % TX, iy = tid / TX;
+  Cx<T> base[RK];
+  if constexpr (H::BAS)
+#pragma unroll
+    for (int k = 0; k < RK; ++k) {
+      const int c1 = t0x + ix, c2 = t0y + iy + k * ROWS;
+      const unsigned i = c1 < n && c2 < m ? (unsigned)(c2 * n + c1) * (unsigned)sizeof(T) : 0u;
+      base[k] = Cx<T>{at32(bs, i), at32(bs + N, i)};
+    }
+  T* pt = pl + t;
+  if constexpr (H::PRO) {   // as the prolongation kernel: x + Pr xc
+    // the coarse values under the box; a value across the period takes its phase as fetch() has it
+    if (tid < H::CB) {
+      const int J1 = wrapm((ox >> 1) + tid % H::CBX, gc.n), J2 = wrapm((oy >> 1) + tid / H::CBX, gc.m);
+      const unsigned i = (unsigned)(J2 * gc.n + J1) * (unsigned)sizeof(T);
+      cl[tid] = at32(cc, i);
+      cl[H::CB + tid] = at32(cc + gc.nm, i);
+    }
+    __syncthreads();
+    const T* q = cl + b * H::CBX + a;
+    const Cx<T> c00{q[0], q[H::CB]};
+    Cx<T> c10{q[1], q[H::CB + 1]}, c01{q[H::CBX], q[H::CB + H::CBX]}, c11{q[H::CBX + 1], q[H::CB + H::CBX + 1]};
+    if (p1 == n - 2) {
+      c10 = cmul(c10, p.ar, p.ai);
+      c11 = cmul(c11, p.ar, p.ai);
+    }
+    if (p2 == m - 2) {
+      c01 = cmul(c01, p.br, p.bi);
+      c11 = cmul(c11, p.br, p.bi);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) u[c] = u[c] + nodal_prolong_combine<T>(c00, c10, c01, c11, c & 1, c >> 1);
+  }
+  if constexpr (!H::ZERO) {
+    if (live)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        pt[c * S::SUB] = u[c].re;
+        pt[S::N + c * S::SUB] = u[c].im;
+      }
+    __syncthreads();
+  }
+  const T inv = (T)1 / (T)st.c0;
+  auto node = [&](auto colour) {
+    constexpr int c = decltype(colour)::value;
+    return BlockNodes<T, S, (c & 1), (c >> 1), CX, CY>{pt, Seam<CX, CY>(p1 + (c & 1), p2 + (c >> 1), n, m), p};
+  };
+  auto pass = [&](auto order) {
+    constexpr int k = decltype(order)::value, c = BWD ? 3 - k : k;
+    constexpr PassRect r = R.r[k];
+    static_assert((r.x0 & 1) == (c & 1) && (r.y0 & 1) == (c >> 1) && r.x0 >= 1 && r.y0 >= 1 && r.x1 <= BX - 2 && r.y1 <= BX - 2,
+                  "pass rectangle");
+    if (live && a >= (r.x0 >> 1) && a <= (r.x1 >> 1) && b >= (r.y0 >> 1) && b <= (r.y1 >> 1)) {
+      const BlockNodes<T, S, (c & 1), (c >> 1), CX, CY, H::ZERO ? c : 4> x{
+          pt, Seam<CX, CY>(p1 + (c & 1), p2 + (c >> 1), n, m), p};
+      const Cx<T> v = rhs[c] - nodal_stencil_at<T>(x, st), o = x.get(0, 0);
+      pt[c * S::SUB] = o.re + inv * v.re;
+      pt[S::N + c * S::SUB] = o.im + inv * v.im;
+    }
+    __syncthreads();
+  };
+  pass(std::integral_constant<int, 0>{});
+  pass(std::integral_constant<int, 1>{});
+  pass(std::integral_constant<int, 2>{});
+  pass(std::integral_constant<int, 3>{});
+#pragma unroll
+  for (int k = 0; k < RK; ++k) {
+    const int c1 = t0x + ix, c2 = t0y + iy + k * ROWS;
+    if (c1 >= n || c2 >= m) continue;
+    const int q = S::at(ix + LO, iy + k * ROWS + LO);
+    const unsigned i = (unsigned)(c2 * n + c1) * (unsigned)sizeof(T);
+    Cx<T> v{pl[q], pl[S::N + q]};
+    if constexpr (H::BAS) v = base[k] + v;   // as the update kernel: base + x
+    at32(xo, i) = v.re;
+    at32(xo + N, i) = v.im;
+  }
+  if constexpr (H::TRES || H::RES) {
+    // the residual b - P x, as the residual kernel computes it, at the nodes of the block in the
+    // tile (TRES), or in the window from one node below and left of it that the restriction to the
+    // tile's coarse nodes reads
+    constexpr int W0 = LO - (H::RES ? 1 : 0), W1 = LO + TX - 1;
+    Cx<T> r[4];
+    auto resid = [&](auto colour) {
+      constexpr int c = decltype(colour)::value;
+      const int bx = 2 * a + (c & 1), by = 2 * b + (c >> 1);
+      r[c] = {0, 0};
+      if (live && bx >= W0 && bx <= W1 && by >= W0 && by <= W1) r[c] = rhs[c] - nodal_stencil_at<T>(node(colour), st);
+    };
+    resid(std::integral_constant<int, 0>{});
+    resid(std::integral_constant<int, 1>{});
+    resid(std::integral_constant<int, 2>{});
+    resid(std::integral_constant<int, 3>{});
+    __syncthreads();   // the iterate has been read: its planes take the residual
+    if (live)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        pt[c * S::SUB] = r[c].re;
+        pt[S::N + c * S::SUB] = r[c].im;
+      }
+    __syncthreads();
+    if constexpr (H::TRES) {
+#pragma unroll
+      for (int k = 0; k < RK; ++k) {
+        const int c1 = t0x + ix, c2 = t0y + iy + k * ROWS;
+        if (c1 >= n || c2 >= m) continue;
+        const int q = S::at(ix + LO, iy + k * ROWS + LO);
+        const unsigned i = (unsigned)(c2 * n + c1) * (unsigned)sizeof(T);
+        at32(ro, i) = pl[q];
+        at32(ro + N, i) = pl[S::N + q];
+      }
+    } else {
+      const int f1 = ox + 2 * a, f2 = oy + 2 * b;
+      if (live && a >= LO / 2 && a < (LO + TX) / 2 && b >= LO / 2 && b < (LO + TX) / 2 && f1 < n && f2 < m) {
+        const Cx<T> v = nodal_restrict_acc<T>(node(std::integral_constant<int, 0>{}));
+        const unsigned J = (unsigned)((f2 >> 1) * gc.n + (f1 >> 1)) * (unsigned)sizeof(T);
+        at32(bco, J) = v.re;
+        at32(bco + gc.nm, J) = v.im;
+      }
+    }
+  }
+}
+
+template <typename T, bool BWD, int MODE>
+__global__ __launch_bounds__(kNodalThreads) void k_nodal_sweep(View<const T> xin, View<T> xout, View<const T> bv, Geo g,
+                                                            const Phase* __restrict__ phs, NodalStencil st,
+                                                            int wide, const int* __restrict__ slots, int ncps,
+                                                            int tiles_x, SweepFuse<T> fz) {
   static_assert(!((MODE & kRestrict) && BWD), "the residual window halo is sized for forward sweeps");
   static_assert(!((MODE & kResid) && !BWD), "the tile residual rides on backward sweeps");
-  constexpr bool RES = (MODE & kRestrict) != 0, PRO = (MODE & kProlong) != 0, BAS = (MODE & kBase) != 0;
-  constexpr bool TRES = (MODE & kResid) != 0;
-  constexpr int LO = RES ? kLoR : kLo;
-  constexpr int HI = TRES ? kHiN + 1 : kHiN;   // (the tile residual: exact one node above / right too)
-  constexpr int BX = TX + LO + HI, BY = TY + LO + HI;
-  using S = Split<BX, BY>;
-  // coarse nodes under the box (prolongating sweeps of boxes inside the period): fine box
-  // position b lies over coarse box position b >> 1 and its neighbours one up
-  constexpr int CBX = (BX - 1) / 2 + 2, CBY = (BY - 1) / 2 + 2, CB = CBX * CBY;
-  __shared__ T pl[2 * S::N];
-  __shared__ T rl[RES ? 2 * (TX + 1) * (TY + 1) : 1];
-  __shared__ T cl[PRO && (sizeof(T) == 4 || TX * TY <= 1024) ? 2 * CB : 1];
-  const TileRef tr = tile_ref(slots, ncps, tiles_x, TX, TY);
-  const int n = g.n, m = g.m, tid = threadIdx.x;
+  static_assert(!((MODE & kZero) && BWD), "the order of the colours in a sweep from zero");
+  using H = NodalShape<T, BWD, MODE>;
+  __shared__ T pl[2 * H::S::N];
+  __shared__ T cl[H::PRO ? 2 * H::CB : 1];
+  const TileRef tr = tile_ref(slots, ncps, tiles_x, H::TX, H::TX);
+  const int n = g.n, m = g.m;
   const int64_t N = g.nm;
-  const int ox = tr.t0x - LO, oy = tr.t0y - LO;
-  const bool cx = !(ox >= 0 && ox + BX <= n), cy = !(oy >= 0 && oy + BY <= m);
+  const int ox = tr.t0x - H::LO, oy = tr.t0y - H::LO;
+  const bool cx = !(ox >= 0 && ox + H::BX <= n), cy = !(oy >= 0 && oy + H::BX <= m);
   const SJ sj{tr.slot, tr.j};
   T* xo = colp(xout, sj, N);
   const T* bc = colp(bv, sj, N);
+  const T* xc = H::ZERO ? nullptr : colp(xin, sj, N);
+  const T* cc = H::PRO ? colp(fz.xc, sj, fz.gc.nm) : nullptr;
+  T* bco = H::RES ? colp(fz.bc, sj, fz.gc.nm) : nullptr;
+  const T* bs = H::BAS ? colp(fz.base, sj, N) : nullptr;
+  T* ro = H::TRES ? colp(fz.res, sj, N) : nullptr;
   const Ph<T> p = cast_phase<T>(phs[tr.slot]);
-  if (zero_start) {
-    for (int e = tid; e < 2 * S::N; e += nthreads()) pl[e] = (T)0;
-  } else {
-    const T* xc = colp(xin, sj, N);
-    const T* cc = PRO ? colp(fz.xc, sj, fz.gc.nm) : nullptr;
-    // (not for FP64 64 x 32 tiles, whose registers would then cost occupancy)
-    constexpr bool STAGE = PRO && (sizeof(T) == 4 || TX * TY <= 1024);
-    if (STAGE && !cx && !cy) {
-      // as the prolongation kernel, x + Pr xc, with the coarse values (as fetch() returns them
-      // at the box's coarse positions, ox and oy being even) staged once in LDS, and the
-      // iterate's loads issued four positions at a time
-      const int J0 = ox >> 1, K0 = oy >> 1;
-      for (int e = tid; e < CB; e += nthreads()) {
-        const Cx<T> v = fetch<T, T>(cc, fz.gc.nm, fz.gc.n, fz.gc.m, 0, J0 + e % CBX, K0 + e / CBX, p);
-        cl[e] = v.re;
-        cl[CB + e] = v.im;
-      }
-      __syncthreads();
-      constexpr int LB = 4;
-      for (int e0 = tid; e0 < BX * BY; e0 += LB * nthreads()) {
-        T ur[LB], ui[LB];
-#pragma unroll
-        for (int u = 0; u < LB; ++u) {
-          const int e = e0 + u * nthreads();
-          if (e >= BX * BY) continue;
-          const int64_t i = (int64_t)(oy + e / BX) * n + ox + e % BX;
-          ur[u] = xc[i];
-          ui[u] = xc[N + i];
-        }
-#pragma unroll
-        for (int u = 0; u < LB; ++u) {
-          const int e = e0 + u * nthreads();
-          if (e >= BX * BY) continue;
-          const int bx = e % BX, by = e / BX;
-          const int q = (by >> 1) * CBX + (bx >> 1);
-          const Cx<T> v = nodal_prolong_combine<T>(Cx<T>{cl[q], cl[CB + q]}, Cx<T>{cl[q + 1], cl[CB + q + 1]},
-                                                   Cx<T>{cl[q + CBX], cl[CB + q + CBX]},
-                                                   Cx<T>{cl[q + CBX + 1], cl[CB + q + CBX + 1]}, bx & 1, by & 1);
-          const int k = S::at(bx, by);
-          pl[k] = ur[u] + v.re;
-          pl[S::N + k] = ui[u] + v.im;
-        }
-      }
-    } else {
-      for (int e = tid; e < BX * BY; e += nthreads()) {
-        const int bx = e % BX, by = e / BX;
-        const int c1 = cx ? wrapm(ox + bx, n) : ox + bx, c2 = cy ? wrapm(oy + by, m) : oy + by;
-        const int64_t i = (int64_t)c2 * n + c1;
-        const int k = S::at(bx, by);
-        if constexpr (PRO) {   // as the prolongation kernel: base + Pr xc
-          const Cx<T> v = nodal_prolong_xy<T>(cc, fz.gc, c1, c2, p);
-          pl[k] = xc[i] + v.re;
-          pl[S::N + k] = xc[N + i] + v.im;
-        } else {
-          pl[k] = xc[i];
-          pl[S::N + k] = xc[N + i];
-        }
-      }
-    }
-  }
-  __syncthreads();
-  // exact margin the residual window (restriction) or the tile residual needs
-  constexpr int EA = RES ? 2 : (TRES ? 1 : 0), EB = (RES || TRES) ? 1 : 0;
-  if (!cx && !cy) nodal_passes<T, BX, BY, BWD, false, false, LO, TX, TY, EA, EB>(pl, bc, st, ox, oy, n, m, N, p);
-  else if (!cy) nodal_passes<T, BX, BY, BWD, true, false, LO, TX, TY, EA, EB>(pl, bc, st, ox, oy, n, m, N, p);
-  else if (!cx) nodal_passes<T, BX, BY, BWD, false, true, LO, TX, TY, EA, EB>(pl, bc, st, ox, oy, n, m, N, p);
-  else nodal_passes<T, BX, BY, BWD, true, true, LO, TX, TY, EA, EB>(pl, bc, st, ox, oy, n, m, N, p);
-  const T* bs = BAS ? colp(fz.base, sj, N) : nullptr;
-  if constexpr (BAS) {   // as the update kernel: base + x (the base loads four positions at a time)
-    constexpr int LB = 4;
-    for (int e0 = tid; e0 < TX * TY; e0 += LB * nthreads()) {
-      T br[LB], bi[LB];
-#pragma unroll
-      for (int u = 0; u < LB; ++u) {
-        const int e = e0 + u * nthreads();
-        const int c1 = tr.t0x + e % TX, c2 = tr.t0y + e / TX;
-        if (e >= TX * TY || c1 >= n || c2 >= m) continue;
-        const int64_t i = (int64_t)c2 * n + c1;
-        br[u] = bs[i];
-        bi[u] = bs[N + i];
-      }
-#pragma unroll
-      for (int u = 0; u < LB; ++u) {
-        const int e = e0 + u * nthreads();
-        const int ix = e % TX, iy = e / TX;
-        const int c1 = tr.t0x + ix, c2 = tr.t0y + iy;
-        if (e >= TX * TY || c1 >= n || c2 >= m) continue;
-        const int k = S::at(ix + LO, iy + LO);
-        const int64_t i = (int64_t)c2 * n + c1;
-        xo[i] = br[u] + pl[k];
-        xo[N + i] = bi[u] + pl[S::N + k];
-      }
-    }
-  } else {
-    for (int e = tid; e < TX * TY; e += nthreads()) {
-      const int ix = e % TX, iy = e / TX;
-      const int c1 = tr.t0x + ix, c2 = tr.t0y + iy;
-      if (c1 >= n || c2 >= m) continue;
-      const int k = S::at(ix + LO, iy + LO);
-      const int64_t i = (int64_t)c2 * n + c1;
-      xo[i] = pl[k];
-      xo[N + i] = pl[S::N + k];
-    }
-  }
-  if constexpr (TRES) {
-    T* ro = colp(fz.res, sj, N);
-    if (!cx && !cy) nodal_tile_resid<T, BX, BY, false, false, LO, TX, TY>(pl, bc, ro, st, ox, oy, n, m, N, p);
-    else if (!cy) nodal_tile_resid<T, BX, BY, true, false, LO, TX, TY>(pl, bc, ro, st, ox, oy, n, m, N, p);
-    else if (!cx) nodal_tile_resid<T, BX, BY, false, true, LO, TX, TY>(pl, bc, ro, st, ox, oy, n, m, N, p);
-    else nodal_tile_resid<T, BX, BY, true, true, LO, TX, TY>(pl, bc, ro, st, ox, oy, n, m, N, p);
-  }
-  if constexpr (RES) {
-    T* bco = colp(fz.bc, sj, fz.gc.nm);
-    if (!cx && !cy)
-      nodal_restrict_tile<T, BX, BY, false, false, LO, TX, TY>(pl, rl, bc, bco, st, ox, oy, tr.t0x, tr.t0y, n, m, N,
-                                                              fz.gc, p);
-    else if (!cy)
-      nodal_restrict_tile<T, BX, BY, true, false, LO, TX, TY>(pl, rl, bc, bco, st, ox, oy, tr.t0x, tr.t0y, n, m, N,
-                                                             fz.gc, p);
-    else if (!cx)
-      nodal_restrict_tile<T, BX, BY, false, true, LO, TX, TY>(pl, rl, bc, bco, st, ox, oy, tr.t0x, tr.t0y, n, m, N,
-                                                             fz.gc, p);
-    else
-      nodal_restrict_tile<T, BX, BY, true, true, LO, TX, TY>(pl, rl, bc, bco, st, ox, oy, tr.t0x, tr.t0y, n, m, N,
-                                                            fz.gc, p);
-  }
+  if (!cx && !cy)
+    nodal_tile<T, BWD, MODE, false, false>(pl, cl, xc, xo, bc, cc, bco, bs, ro, st, tr.t0x, tr.t0y, n, m, N, fz.gc, p, wide != 0);
+  else if (!cy)
+    nodal_tile<T, BWD, MODE, true, false>(pl, cl, xc, xo, bc, cc, bco, bs, ro, st, tr.t0x, tr.t0y, n, m, N, fz.gc, p, wide != 0);
+  else if (!cx)
+    nodal_tile<T, BWD, MODE, false, true>(pl, cl, xc, xo, bc, cc, bco, bs, ro, st, tr.t0x, tr.t0y, n, m, N, fz.gc, p, wide != 0);
+  else
+    nodal_tile<T, BWD, MODE, true, true>(pl, cl, xc, xo, bc, cc, bco, bs, ro, st, tr.t0x, tr.t0y, n, m, N, fz.gc, p, wide != 0);
 }
 
-// Tile shapes (nodes): 0: 32 x 32, 1: 64 x 32.  FP64 edge sweeps, and FP64 nodal sweeps with
-// the residual window, use 32 x 32 only (the larger boxes exceed the static LDS limit).
+// Edge tile shapes (nodes): 0: 32 x 32, 1: 64 x 32 (FP32; the FP64 box exceeds the static LDS limit).
 // 512 threads when the launch has fewer than four tile workgroups per compute unit
 inline unsigned sweep_threads(const dim3& grid) { return (uint64_t)grid.x * grid.y < 1024 ? 512u : 256u; }
 
@@ -833,42 +779,14 @@ void edge_launch(View<const T> xin, View<T> xout, View<const T> b, const EdgeArg
   edge_go<T, TX, TY, false, 0>(xin, xout, b, a, g, ph, mu, zero_start, fz, L);
 }
 
-template <typename T, int TX, int TY, bool BWD, int MODE>
+template <typename T, bool BWD, int MODE>
 void nodal_go(View<const T> xin, View<T> xout, View<const T> b, const Geo& g, const Phase* ph, const NodalStencil& c,
-              bool zero_start, const SweepFuse<T>& fz, const Launch& L) {
-  const int tx = (g.n + TX - 1) / TX, ty = (g.m + TY - 1) / TY;
+              const SweepFuse<T>& fz, const Launch& L) {
+  const int tx = (g.n + kNodalTile - 1) / kNodalTile, ty = (g.m + kNodalTile - 1) / kNodalTile;
   dim3 grid((unsigned)(tx * ty), (unsigned)(L.nact * L.ncps));
-  k_nodal_sweep<T, TX, TY, BWD, MODE><<<grid, sweep_threads(grid), 0, L.st>>>(xin, xout, b, g, ph, c, zero_start ? 1 : 0,
-                                                                   L.slots, L.ncps, tx, fz);
-}
-
-template <typename T, int TX, int TY>
-void nodal_launch(View<const T> xin, View<T> xout, View<const T> b, const Geo& g, const Phase* ph,
-                  const NodalStencil& c, bool backward, bool zero_start, const SweepFuse<T>& fz, const Launch& L) {
-  const int mode = (fz.bc.p ? kRestrict : 0) | (fz.xc.p ? kProlong : 0) | (fz.base.p ? kBase : 0) |
-                   (fz.res.p ? kResid : 0);
-  if (!backward) {
-    if constexpr (sizeof(T) == 4 || TX * TY <= 1024) {   // (the FP64 64 x 32 window is routed to 32 x 32)
-      if (mode == kRestrict) {
-        nodal_go<T, TX, TY, false, kRestrict>(xin, xout, b, g, ph, c, zero_start, fz, L);
-        return;
-      }
-    }
-    nodal_go<T, TX, TY, false, 0>(xin, xout, b, g, ph, c, zero_start, fz, L);
-    return;
-  }
-  switch (mode) {
-    case kProlong: nodal_go<T, TX, TY, true, kProlong>(xin, xout, b, g, ph, c, zero_start, fz, L); break;
-    case kBase: nodal_go<T, TX, TY, true, kBase>(xin, xout, b, g, ph, c, zero_start, fz, L); break;
-    case kProlong | kBase:
-      nodal_go<T, TX, TY, true, kProlong | kBase>(xin, xout, b, g, ph, c, zero_start, fz, L);
-      break;
-    case kProlong | kResid:
-      nodal_go<T, TX, TY, true, kProlong | kResid>(xin, xout, b, g, ph, c, zero_start, fz, L);
-      break;
-    case kResid: nodal_go<T, TX, TY, true, kResid>(xin, xout, b, g, ph, c, zero_start, fz, L); break;
-    default: nodal_go<T, TX, TY, true, 0>(xin, xout, b, g, ph, c, zero_start, fz, L); break;
-  }
+  // two values a load where the columns (whole numbers of pairs) start on a pair
+  const bool wide = (((uintptr_t)b.p | (uintptr_t)xin.p) & (2 * sizeof(T) - 1)) == 0;
+  k_nodal_sweep<T, BWD, MODE><<<grid, kNodalThreads, 0, L.st>>>(xin, xout, b, g, ph, c, wide ? 1 : 0, L.slots, L.ncps, tx, fz);
 }
 
 }  // namespace
@@ -892,18 +810,30 @@ void edge_sweep(View<const T> xin, View<T> xout, View<const T> b, const double* 
 
 template <typename T>
 void nodal_sweep(View<const T> xin, View<T> xout, View<const T> b, const Geo& g, const Phase* ph,
-                 const NodalStencil& c, bool backward, bool zero_start, int tile, const Launch& L,
-                 const SweepFuse<T>& fz) {
+                 const NodalStencil& c, bool backward, bool zero_start, const Launch& L, const SweepFuse<T>& fz) {
   if (L.nact * L.ncps == 0) return;
-  if (tile == 1 && (sizeof(T) == 4 || !fz.bc.p))
-    nodal_launch<T, 64, 32>(xin, xout, b, g, ph, c, backward, zero_start, fz, L);
-  else
-    nodal_launch<T, 32, 32>(xin, xout, b, g, ph, c, backward, zero_start, fz, L);
+  const int mode = (fz.bc.p ? kRestrict : 0) | (fz.xc.p ? kProlong : 0) | (fz.base.p ? kBase : 0) |
+                   (fz.res.p ? kResid : 0);
+  if (!backward) {
+    if (mode == kRestrict && zero_start) nodal_go<T, false, kRestrict | kZero>(xin, xout, b, g, ph, c, fz, L);
+    else if (mode == kRestrict) nodal_go<T, false, kRestrict>(xin, xout, b, g, ph, c, fz, L);
+    else if (zero_start) nodal_go<T, false, kZero>(xin, xout, b, g, ph, c, fz, L);
+    else nodal_go<T, false, 0>(xin, xout, b, g, ph, c, fz, L);
+    return;
+  }
+  switch (mode) {
+    case kProlong: nodal_go<T, true, kProlong>(xin, xout, b, g, ph, c, fz, L); break;
+    case kBase: nodal_go<T, true, kBase>(xin, xout, b, g, ph, c, fz, L); break;
+    case kProlong | kBase: nodal_go<T, true, kProlong | kBase>(xin, xout, b, g, ph, c, fz, L); break;
+    case kProlong | kResid: nodal_go<T, true, kProlong | kResid>(xin, xout, b, g, ph, c, fz, L); break;
+    case kResid: nodal_go<T, true, kResid>(xin, xout, b, g, ph, c, fz, L); break;
+    default: nodal_go<T, true, 0>(xin, xout, b, g, ph, c, fz, L); break;
+  }
 }
 
 template void edge_sweep<double>(View<const double>, View<double>, View<const double>, const double*, const float*, const double*, const float*, const Geo&, const Phase*, const double*, const PatchT&, bool, bool, int, const Launch&, const SweepFuse<double>&);
 template void edge_sweep<float>(View<const float>, View<float>, View<const float>, const double*, const float*, const double*, const float*, const Geo&, const Phase*, const double*, const PatchT&, bool, bool, int, const Launch&, const SweepFuse<float>&);
-template void nodal_sweep<double>(View<const double>, View<double>, View<const double>, const Geo&, const Phase*, const NodalStencil&, bool, bool, int, const Launch&, const SweepFuse<double>&);
-template void nodal_sweep<float>(View<const float>, View<float>, View<const float>, const Geo&, const Phase*, const NodalStencil&, bool, bool, int, const Launch&, const SweepFuse<float>&);
+template void nodal_sweep<double>(View<const double>, View<double>, View<const double>, const Geo&, const Phase*, const NodalStencil&, bool, bool, const Launch&, const SweepFuse<double>&);
+template void nodal_sweep<float>(View<const float>, View<float>, View<const float>, const Geo&, const Phase*, const NodalStencil&, bool, bool, const Launch&, const SweepFuse<float>&);
 
 }  // namespace bl
