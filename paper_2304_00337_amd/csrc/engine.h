@@ -196,7 +196,6 @@ struct bl_solver {
   bl::SmoothShape tune_edge, tune_nodal;
   int tune_rr = 0;            // Rayleigh-Ritz output tile for q = 2p (0 = by padding)
   double tune_ms = 0.0;       // time the autotuner spent
-  int tune_sweep = 0;         // tile shape of the edge sweeps (see edge_sweep)
 };
 
 namespace bl {

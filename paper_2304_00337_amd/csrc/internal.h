@@ -141,18 +141,13 @@ struct SweepFuse {
 };
 
 // One whole smoothing sweep (four colours; reverse colour order when backward) as one launch
-// over LDS tiles with halos, bit-identical to the four colour launches; `tile` selects the
-// edge sweeps' tile shape (0: 32 x 32, 1: 64 x 32 nodes; FP64 32 x 32).  Reads the iterate
+// over LDS tiles with halos, bit-identical to the four colour launches.  Reads the iterate
 // from xin and writes it to xout, which must be different buffers; zero_start: the iterate is
 // zero on entry (xin is then not read).  sweep.hip.
 template <typename T>
 void edge_sweep(View<const T> xin, View<T> xout, View<const T> b, const double* kappa64, const float* kappa32,
                 const double* sinv64, const float* sinv32, const Geo& g, const Phase* ph, const double* mu,
-                const PatchT& T4, bool backward, bool zero_start, int tile, const Launch& L,
-                const SweepFuse<T>& fz = SweepFuse<T>{});
-// Whether edge sweeps of this element size can restrict (SweepFuse::bc): FP32 only (the
-// FP64 residual window exceeds the static LDS of a workgroup).
-bool edge_sweep_restricts(size_t elem);
+                bool backward, bool zero_start, const Launch& L, const SweepFuse<T>& fz = SweepFuse<T>{});
 template <typename T>
 void nodal_sweep(View<const T> xin, View<T> xout, View<const T> b, const Geo& g, const Phase* ph,
                  const NodalStencil& c, bool backward, bool zero_start, const Launch& L,

@@ -341,7 +341,7 @@ void vcycle_edge(bl_solver* s, int l, View<const T> b, View<T> x, const Launch& 
   const int ncols = L.nact * L.ncps;
   const int npre = s->opts.nu_pre, npost = s->opts.nu_post;
   View<T> r = view(static_cast<T*>(lv.er[pr]), lv.ecap[pr]);
-  if (s->opts.tiled_sweeps == 2 && npre > 0 && npost > 0 && edge_sweep_restricts(sizeof(T))) {
+  if (s->opts.tiled_sweeps == 2 && npre > 0 && npost > 0) {
     // transfers folded into the sweeps, as in the nodal cycle (x and r alternate as sweep
     // buffers; the pre-smoothed iterate lands in E so that the last post-sweep writes x)
     Level& C = s->lv[l + 1];
@@ -357,8 +357,8 @@ void vcycle_edge(bl_solver* s, int l, View<const T> b, View<T> x, const Launch& 
         fz.gc = C.g;
       }
       timing_begin(s, l);
-      edge_sweep<T>(cv(prev), dst, b, lv.kappa64, lv.kappa32, lv.sinv64, lv.sinv32, lv.g, s->ph_d, s->mu_d, lv.T4,
-                    false, it == 0, s->tune_sweep, L, fz);
+      edge_sweep<T>(cv(prev), dst, b, lv.kappa64, lv.kappa32, lv.sinv64, lv.sinv32, lv.g, s->ph_d, s->mu_d,
+                    false, it == 0, L, fz);
       timing_end(s, l, ncols, smooth_bytes(lv.g, sizeof(T), true, it == 0, ncols, L.nact, fz.bc.p ? 0.25 : 0.0));
       prev = dst;
     }
@@ -371,8 +371,8 @@ void vcycle_edge(bl_solver* s, int l, View<const T> b, View<T> x, const Launch& 
         fz.gc = C.g;
       }
       timing_begin(s, l);
-      edge_sweep<T>(cv(prev), dst, b, lv.kappa64, lv.kappa32, lv.sinv64, lv.sinv32, lv.g, s->ph_d, s->mu_d, lv.T4,
-                    true, false, s->tune_sweep, L, fz);
+      edge_sweep<T>(cv(prev), dst, b, lv.kappa64, lv.kappa32, lv.sinv64, lv.sinv32, lv.g, s->ph_d, s->mu_d,
+                    true, false, L, fz);
       timing_end(s, l, ncols, smooth_bytes(lv.g, sizeof(T), true, false, ncols, L.nact, it == 0 ? 0.25 : 0.0));
       prev = dst;
     }
@@ -389,8 +389,8 @@ void vcycle_edge(bl_solver* s, int l, View<const T> b, View<T> x, const Launch& 
       View<T> src = ((npre - it) % 2 == 0) ? x : r;   // the previous sweep's output
       View<T> dst = ((npre - 1 - it) % 2 == 0) ? x : r;
       timing_begin(s, l);
-      edge_sweep<T>(cv(src), dst, b, lv.kappa64, lv.kappa32, lv.sinv64, lv.sinv32, lv.g, s->ph_d, s->mu_d, lv.T4,
-                    false, it == 0, s->tune_sweep, L);
+      edge_sweep<T>(cv(src), dst, b, lv.kappa64, lv.kappa32, lv.sinv64, lv.sinv32, lv.g, s->ph_d, s->mu_d,
+                    false, it == 0, L);
       timing_end(s, l, ncols, smooth_bytes(lv.g, sizeof(T), true, it == 0, ncols, L.nact));
       nl_launch += 1;
       continue;
@@ -414,8 +414,8 @@ void vcycle_edge(bl_solver* s, int l, View<const T> b, View<T> x, const Launch& 
     for (int it = 0; it < npost; ++it) {
       View<T> dst = (cur.p == x.p && cur.off == x.off && cur.cps == x.cps) ? r : x;
       timing_begin(s, l);
-      edge_sweep<T>(cv(cur), dst, b, lv.kappa64, lv.kappa32, lv.sinv64, lv.sinv32, lv.g, s->ph_d, s->mu_d, lv.T4,
-                    true, false, s->tune_sweep, L);
+      edge_sweep<T>(cv(cur), dst, b, lv.kappa64, lv.kappa32, lv.sinv64, lv.sinv32, lv.g, s->ph_d, s->mu_d,
+                    true, false, L);
       timing_end(s, l, ncols, smooth_bytes(lv.g, sizeof(T), true, false, ncols, L.nact));
       cur = dst;
       nl_launch += 1;
@@ -1611,8 +1611,8 @@ int apply_t(bl_solver* s, int op, int level, int ncols, const void* xv, const vo
       if (xv == outv) return set_error(BL_EINVAL, "a sweep reads x and writes out: different blocks required%s");
       const bool back = op == BL_OP_EDGE_SWEEP_BACK || op == BL_OP_NODAL_SWEEP_BACK;
       if (op == BL_OP_EDGE_SWEEP || op == BL_OP_EDGE_SWEEP_BACK)
-        edge_sweep<T>(x, out, y, L.kappa64, L.kappa32, L.sinv64, L.sinv32, L.g, s->ph_d, s->mu_d, L.T4, back, false,
-                      s->tune_sweep, La);
+        edge_sweep<T>(x, out, y, L.kappa64, L.kappa32, L.sinv64, L.sinv32, L.g, s->ph_d, s->mu_d, back, false,
+                      La);
       else
         nodal_sweep<T>(x, out, y, L.g, s->ph_d, s->ns, back, false, La);
       break;

@@ -148,6 +148,17 @@ __device__ __forceinline__ Cx<T> patch_resid(Cx<T> b, T ka, Cx<T> wa, T kb, Cx<T
   return b - cfma<T>(s, c, mm, mass);
 }
 
+// x += W r on a patch's edges (W's 10 upper-triangle entries at w).
+template <typename T, typename XA>
+__device__ __forceinline__ void patch_solve(const XA& X, const T* w, Cx<T> r0, Cx<T> r1, Cx<T> r2, Cx<T> r3) {
+  const T w00 = w[0], w01 = w[1], w02 = w[2], w03 = w[3], w11 = w[4], w12 = w[5], w13 = w[6], w22 = w[7],
+          w23 = w[8], w33 = w[9];
+  X.add(0, 0, 0, cfma<T>(w03, r3, cfma<T>(w02, r2, cfma<T>(w01, r1, w00 * r0))));
+  X.add(0, -1, 0, cfma<T>(w13, r3, cfma<T>(w12, r2, cfma<T>(w11, r1, w01 * r0))));
+  X.add(1, 0, 0, cfma<T>(w23, r3, cfma<T>(w22, r2, cfma<T>(w12, r1, w02 * r0))));
+  X.add(1, 0, -1, cfma<T>(w33, r3, cfma<T>(w23, r2, cfma<T>(w13, r1, w03 * r0))));
+}
+
 // Stabilised node-patch update at node (p1, p2) (Section 5): residual r of K = A + mu M on
 // the four patch edges, delta = W r with the node's patch inverse W = T diag(1/mu, S^{-1})
 // T^T (10 upper-triangle entries at w), x += delta.  k* are the kappas of the four cells
@@ -176,12 +187,7 @@ __device__ __forceinline__ void patch_update(const XA& X, const BA& B, T kne, T 
   const Cx<T> r1 = patch_resid<T>(B.get(0, -1, 0), ksw, wsw, knw, wnw, s, mmx, Xm0, Xm1, Xmm);
   const Cx<T> r2 = patch_resid<T>(B.get(1, 0, 0), kne, wne, knw, wnw, s, mmy, Y00, Y10, Ym0);
   const Cx<T> r3 = patch_resid<T>(B.get(1, 0, -1), kse, wse, ksw, wsw, s, mmy, Y0m, Y1m, Ymm);
-  const T w00 = w[0], w01 = w[1], w02 = w[2], w03 = w[3], w11 = w[4], w12 = w[5], w13 = w[6], w22 = w[7],
-          w23 = w[8], w33 = w[9];
-  X.add(0, 0, 0, cfma<T>(w03, r3, cfma<T>(w02, r2, cfma<T>(w01, r1, w00 * r0))));
-  X.add(0, -1, 0, cfma<T>(w13, r3, cfma<T>(w12, r2, cfma<T>(w11, r1, w01 * r0))));
-  X.add(1, 0, 0, cfma<T>(w23, r3, cfma<T>(w22, r2, cfma<T>(w12, r1, w02 * r0))));
-  X.add(1, 0, -1, cfma<T>(w33, r3, cfma<T>(w23, r2, cfma<T>(w13, r1, w03 * r0))));
+  patch_solve<T>(X, w, r0, r1, r2, r3);
 }
 
 // The patch update on a column in memory.

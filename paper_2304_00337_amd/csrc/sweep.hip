@@ -35,10 +35,6 @@ namespace {
 constexpr int kLo = 4;    // halo below / left of a tile, nodes (even: keeps colour parity)
 constexpr int kHiE = 5;   // halo above / right, edge sweeps
 constexpr int kHiN = 4;   // halo above / right, nodal sweeps
-constexpr int kMaxThreads = 512;   // workgroups of 256 threads, or 512 where the launch has few tiles
-// (a colour pass of a 32 x 32 tile then takes one round instead of two: the coarser levels'
-// launches are too small to hide the rounds' latency behind other workgroups)
-__device__ __forceinline__ int nthreads() { return (int)blockDim.x; }
 
 // MODE bits of a sweep with level transfers folded in: kRestrict (forward sweeps) also forms
 // the residual of the result and restricts it to the coarse right-hand side; kProlong starts
@@ -106,50 +102,6 @@ __device__ __forceinline__ Cx<T> phased(Cx<T> v, int d1, int d2, const Seam<CX, 
   if (CY && d2 != 0) v = pick(sm.cross_y(d2), cmul(v, p.br, d2 > 0 ? p.bi : -p.bi), v);
   return v;
 }
-
-// Iterate around the patch node at box position (2i + PX, 2j + PY) = canonical (p1, p2), in
-// the LDS planes (x-edge re, x-edge im, y-edge re, y-edge im, Split::N values each).
-template <typename T, int BX, int BY, int PX, int PY, bool CX, bool CY>
-struct TileEdges {
-  using S = Split<BX, BY>;
-  T* pl;
-  int i, j;
-  Seam<CX, CY> sm;
-  Ph<T> p;
-  __device__ __forceinline__ int idx(int d1, int d2) const {
-    const int sx = (PX + d1) & 1, sy = (PY + d2) & 1;
-    return (sx + 2 * sy) * S::SUB + (j + ((PY + d2) >> 1)) * S::HX + i + ((PX + d1) >> 1);
-  }
-  __device__ __forceinline__ Cx<T> get(int c, int d1, int d2) const {
-    const T* q = pl + c * 2 * S::N + idx(d1, d2);
-    return phased<CX, CY, T>(Cx<T>{q[0], q[S::N]}, d1, d2, sm, p);
-  }
-  // as add_ext(): a value written one period back is stored times alpha (beta)
-  __device__ __forceinline__ void add(int c, int d1, int d2, Cx<T> v) const {
-    if (CX && d1 < 0) v = pick(sm.lx, cmul(v, p.ar, p.ai), v);
-    if (CY && d2 < 0) v = pick(sm.ly, cmul(v, p.br, p.bi), v);
-    T* q = pl + c * 2 * S::N + idx(d1, d2);
-    q[0] = q[0] + v.re;
-    q[S::N] = q[S::N] + v.im;
-  }
-};
-
-// Right-hand side around the patch node, read in memory (as fetch()).
-template <typename T, bool CX, bool CY>
-struct TileRhs {
-  const T* bc;
-  int64_t N, nm;
-  int n, m, p1, p2;
-  Seam<CX, CY> sm;
-  Ph<T> p;
-  __device__ __forceinline__ Cx<T> get(int c, int d1, int d2) const {
-    int j1 = p1 + d1, j2 = p2 + d2;
-    if (CX && d1 != 0) j1 = sm.cross_x(d1) ? (d1 < 0 ? n - 1 : 0) : j1;
-    if (CY && d2 != 0) j2 = sm.cross_y(d2) ? (d2 < 0 ? m - 1 : 0) : j2;
-    const int64_t k = (c ? nm : 0) + (int64_t)j2 * n + j1;
-    return phased<CX, CY, T>(Cx<T>{bc[k], bc[N + k]}, d1, d2, sm, p);
-  }
-};
 
 // Patches each colour pass has to update.  Walking the passes backwards from the region that
 // must be exact after the sweep (the tile, or the residual window's inputs), a pass needs the
@@ -235,315 +187,12 @@ struct EdgeArgs {
   const float* k32;
   const double* si64;
   const float* si32;
-  PatchT T4;
   double s, mx, my;
 };
 
-// One colour pass of the edge smoother on the box (patch nodes at box positions 1 .. B-2 of
-// the colour's parity; the box origin t0 - kLo is even and n, m are even, so the parity of a
-// position is that of its canonical node).
-template <typename T, int BX, int BY, int COLOUR, bool CX, bool CY, int X0, int X1, int Y0, int Y1>
-__device__ __forceinline__ void edge_pass(T* pl, const T* bc, const EdgeArgs& a, int slot, int ox, int oy, int n,
-                                          int m, int64_t N, int64_t nm, T mu, const Ph<T>& p) {
-  constexpr int PX = COLOUR & 1, PY = COLOUR >> 1;
-  static_assert((X0 & 1) == PX && (Y0 & 1) == PY && X0 >= 1 && Y0 >= 1 && X1 <= BX - 2 && Y1 <= BY - 2, "pass rectangle");
-  constexpr int B0X = X0, B0Y = Y0;
-  constexpr int CNX = (X1 - X0) / 2 + 1, CNY = (Y1 - Y0) / 2 + 1;
-  const double* k64 = a.k64 + (int64_t)slot * nm;
-  const float* k32 = a.k32 + (int64_t)slot * nm;
-  const T* sib = pick_si<T>(a.si64, a.si32) + kPatchW * (int64_t)slot * nm;
-  const T s = (T)a.s;
-  const T mmx = mu * (T)a.mx, mmy = mu * (T)a.my;
-  for (int t = threadIdx.x; t < CNX * CNY; t += nthreads()) {
-    const int i = (B0X >> 1) + t % CNX, j = (B0Y >> 1) + t / CNX;
-    const int bx = 2 * i + PX, by = 2 * j + PY;
-    const int p1 = CX ? wrapm(ox + bx, n) : ox + bx;
-    const int p2 = CY ? wrapm(oy + by, m) : oy + by;
-    const T* si = sib + kPatchW * ((int64_t)p2 * n + p1);
-    const Seam<CX, CY> sm(p1, p2, n, m);
-    const TileEdges<T, BX, BY, PX, PY, CX, CY> X{pl, i, j, sm, p};
-    const int p1m = wrapi(p1 - 1, n), p2m = wrapi(p2 - 1, m);
-    const T kne = kap<T>(k64, k32, (int64_t)p2 * n + p1);
-    const T knw = kap<T>(k64, k32, (int64_t)p2 * n + p1m);
-    const T ksw = kap<T>(k64, k32, (int64_t)p2m * n + p1m);
-    const T kse = kap<T>(k64, k32, (int64_t)p2m * n + p1);
-    const TileRhs<T, CX, CY> B{bc, N, nm, n, m, p1, p2, sm, p};
-    patch_update<T>(X, B, kne, knw, ksw, kse, si, s, mmx, mmy);
-  }
-}
-
-template <typename T, int BX, int BY, bool BWD, bool CX, bool CY, int LO, int TX, int TY, int EA, int EB>
-__device__ __forceinline__ void edge_passes(T* pl, const T* bc, const EdgeArgs& a, int slot, int ox, int oy, int n,
-                                            int m, int64_t N, int64_t nm, T mu, const Ph<T>& p) {
-  constexpr SweepRects R = sweep_rects(true, BX, BY, LO, TX, TY, EA, EB, BWD);
-  static_assert(R.ok, "the halo does not cover the sweep's dependency cone");
-#define BL_EPASS(k, c)                                                                                             \
-  edge_pass<T, BX, BY, c, CX, CY, R.r[k].x0, R.r[k].x1, R.r[k].y0, R.r[k].y1>(pl, bc, a, slot, ox, oy, n, m, N, nm, mu, \
-                                                                            p);                                       \
-  __syncthreads();
-  BL_EPASS(0, BWD ? 3 : 0)
-  BL_EPASS(1, BWD ? 2 : 1)
-  BL_EPASS(2, BWD ? 1 : 2)
-  BL_EPASS(3, BWD ? 0 : 3)
-#undef BL_EPASS
-}
-
-// Residual b - (A + mu M) x at both edges owned by the box positions of parity (PX, PY)
-// inside the residual window (as the residual kernel computes them), into rl (row-major
-// window; planes x re, x im, y re, y im).
-template <typename T, int BX, int BY, int PX, int PY, bool CX, bool CY, int LO, int TX, int TY>
-__device__ __forceinline__ void edge_resid_pass(T* pl, T* rl, const T* bc, const EdgeArgs& a, int slot, int ox,
-                                                int oy, int n, int m, int64_t N, int64_t nm, T mu, const Ph<T>& p) {
-  constexpr int R0 = LO - 1, RW = TX + 1, RH = TY + 1, RP = RW * RH;
-  constexpr int I0 = (R0 - PX + 1) / 2, I1 = (LO + TX - 1 - PX) / 2;
-  constexpr int J0 = (R0 - PY + 1) / 2, J1 = (LO + TY - 1 - PY) / 2;
-  constexpr int CNX = I1 - I0 + 1, CNY = J1 - J0 + 1;
-  const double* k64 = a.k64 + (int64_t)slot * nm;
-  const float* k32 = a.k32 + (int64_t)slot * nm;
-  const T s = (T)a.s, mx = (T)a.mx, my = (T)a.my;
-  for (int t = threadIdx.x; t < CNX * CNY; t += nthreads()) {
-    const int i = I0 + t % CNX, j = J0 + t / CNX;
-    const int bx = 2 * i + PX, by = 2 * j + PY;
-    const int p1 = CX ? wrapm(ox + bx, n) : ox + bx;
-    const int p2 = CY ? wrapm(oy + by, m) : oy + by;
-    const int64_t k = (int64_t)p2 * n + p1;
-    const TileEdges<T, BX, BY, PX, PY, CX, CY> X{pl, i, j, Seam<CX, CY>(p1, p2, n, m), p};
-    const T kh = kap<T>(k64, k32, k);
-    const int q = (by - R0) * RW + (bx - R0);
-    Cx<T> Au, Mu;
-    edge_AM_acc<T>(X, 0, kap<T>(k64, k32, (int64_t)wrapi(p2 - 1, m) * n + p1), kh, s, mx, Au, Mu);
-    const Cx<T> rx = Cx<T>{bc[k], bc[N + k]} - (Au + (mu * Mu));
-    edge_AM_acc<T>(X, 1, kh, kap<T>(k64, k32, (int64_t)p2 * n + wrapi(p1 - 1, n)), s, my, Au, Mu);
-    const Cx<T> ry = Cx<T>{bc[nm + k], bc[N + nm + k]} - (Au + (mu * Mu));
-    rl[q] = rx.re;
-    rl[RP + q] = rx.im;
-    rl[2 * RP + q] = ry.re;
-    rl[3 * RP + q] = ry.im;
-  }
-}
-
-// Residual window values of component c around window position (x, y) (as fetch()).
-template <typename T, int RW, int RH, bool CX, bool CY>
-struct WindowEdges {
-  const T* rl;
-  int x, y;
-  Seam<CX, CY> sm;
-  Ph<T> p;
-  __device__ __forceinline__ Cx<T> get(int c, int d1, int d2) const {
-    const int q = c * 2 * RW * RH + (y + d2) * RW + x + d1;
-    return phased<CX, CY, T>(Cx<T>{rl[q], rl[RW * RH + q]}, d1, d2, sm, p);
-  }
-};
-
-// Residual of the swept tile and its restriction to the edges of the tile's coarse nodes.
-template <typename T, int BX, int BY, bool CX, bool CY, int LO, int TX, int TY>
-__device__ __forceinline__ void edge_restrict_tile(T* pl, T* rl, const T* bc, T* bco, const EdgeArgs& a,
-                                                   int slot, int ox, int oy, int t0x, int t0y, int n, int m,
-                                                   int64_t N, int64_t nm, T mu, const Geo& gc, const Ph<T>& p) {
-  edge_resid_pass<T, BX, BY, 0, 0, CX, CY, LO, TX, TY>(pl, rl, bc, a, slot, ox, oy, n, m, N, nm, mu, p);
-  edge_resid_pass<T, BX, BY, 1, 0, CX, CY, LO, TX, TY>(pl, rl, bc, a, slot, ox, oy, n, m, N, nm, mu, p);
-  edge_resid_pass<T, BX, BY, 0, 1, CX, CY, LO, TX, TY>(pl, rl, bc, a, slot, ox, oy, n, m, N, nm, mu, p);
-  edge_resid_pass<T, BX, BY, 1, 1, CX, CY, LO, TX, TY>(pl, rl, bc, a, slot, ox, oy, n, m, N, nm, mu, p);
-  __syncthreads();
-  constexpr int HX = TX / 2, HY = TY / 2;
-  for (int t = threadIdx.x; t < HX * HY; t += nthreads()) {
-    const int jx = t % HX, jy = t / HX;
-    const int f1 = t0x + 2 * jx, f2 = t0y + 2 * jy;
-    if (f1 >= n || f2 >= m) continue;
-    const WindowEdges<T, TX + 1, TY + 1, CX, CY> R{rl, 2 * jx + 1, 2 * jy + 1, Seam<CX, CY>(f1, f2, n, m), p};
-    const int64_t J = (int64_t)(f2 >> 1) * gc.n + (f1 >> 1);
-    const Cx<T> vx = edge_restrict_acc<T>(R, 0);
-    const Cx<T> vy = edge_restrict_acc<T>(R, 1);
-    bco[J] = vx.re;
-    bco[gc.ne + J] = vx.im;
-    bco[gc.nm + J] = vy.re;
-    bco[gc.ne + gc.nm + J] = vy.im;
-  }
-}
-
-template <typename T, int TX, int TY, bool BWD, int MODE>
-__global__ __launch_bounds__(kMaxThreads) void k_edge_sweep(View<const T> xin, View<T> xout, View<const T> bv, EdgeArgs a,
-                                                         Geo g, const Phase* __restrict__ phs,
-                                                         const double* __restrict__ mus, int zero_start,
-                                                         const int* __restrict__ slots, int ncps, int tiles_x,
-                                                         SweepFuse<T> fz) {
-  static_assert(!((MODE & kRestrict) && BWD), "the residual window halo is sized for forward sweeps");
-  static_assert(!(MODE & kBase), "edge sweeps have no base update");
-  constexpr bool RES = (MODE & kRestrict) != 0, PRO = (MODE & kProlong) != 0;
-  constexpr int LO = RES ? kLoR : kLo;
-  constexpr int BX = TX + LO + (RES ? kHiER : kHiE), BY = TY + LO + (RES ? kHiER : kHiE);
-  using S = Split<BX, BY>;
-  // coarse edges under the box (prolongating sweeps of boxes inside the period, FP32): fine box
-  // position b lies over coarse box position b >> 1 and its neighbours one up
-  constexpr bool STAGE = PRO && sizeof(T) == 4;
-  constexpr int CBX = (BX - 1) / 2 + 2, CBY = (BY - 1) / 2 + 2, CB = CBX * CBY;
-  __shared__ T pl[4 * S::N];
-  __shared__ T rl[RES ? 4 * (TX + 1) * (TY + 1) : 1];
-  __shared__ T cl[STAGE ? 4 * CB : 1];   // x-edge re, im, y-edge re, im
-  const TileRef tr = tile_ref(slots, ncps, tiles_x, TX, TY);
-  const int n = g.n, m = g.m, tid = threadIdx.x;
-  const int64_t N = g.ne, nm = g.nm;
-  const int ox = tr.t0x - LO, oy = tr.t0y - LO;   // canonical node of box position 0 (unwrapped)
-  const bool cx = !(ox >= 0 && ox + BX <= n), cy = !(oy >= 0 && oy + BY <= m);
-  const SJ sj{tr.slot, tr.j};
-  T* xo = colp(xout, sj, N);
-  const T* bc = colp(bv, sj, N);
-  const Ph<T> p = cast_phase<T>(phs[tr.slot]);
-  if (zero_start) {
-    for (int e = tid; e < 4 * S::N; e += nthreads()) pl[e] = (T)0;
-  } else {
-    const T* xc = colp(xin, sj, N);
-    const T* cc = PRO ? colp(fz.xc, sj, fz.gc.ne) : nullptr;
-    if (STAGE && !cx && !cy) {
-      // as the prolongation kernel, x + Pr xc, with the coarse edges (as fetch() returns them
-      // at the box's coarse positions, ox and oy being even) staged once in LDS, and the
-      // iterate's loads issued four positions at a time
-      const Geo& gc = fz.gc;
-      const int J0 = ox >> 1, K0 = oy >> 1;
-      for (int e = tid; e < CB; e += nthreads()) {
-        const int a = e % CBX, b = e / CBX;
-        const Cx<T> vx = fetch<T, T>(cc, gc.ne, gc.n, gc.m, 0, J0 + a, K0 + b, p);
-        const Cx<T> vy = fetch<T, T>(cc, gc.ne, gc.n, gc.m, gc.nm, J0 + a, K0 + b, p);
-        cl[e] = vx.re;
-        cl[CB + e] = vx.im;
-        cl[2 * CB + e] = vy.re;
-        cl[3 * CB + e] = vy.im;
-      }
-      __syncthreads();
-      constexpr int LB = 4;
-      for (int e0 = tid; e0 < BX * BY; e0 += LB * nthreads()) {
-        T u[LB][4];
-#pragma unroll
-        for (int v = 0; v < LB; ++v) {
-          const int e = e0 + v * nthreads();
-          if (e >= BX * BY) continue;
-          const int64_t i = (int64_t)(oy + e / BX) * n + ox + e % BX;
-          u[v][0] = xc[i];
-          u[v][1] = xc[N + i];
-          u[v][2] = xc[nm + i];
-          u[v][3] = xc[N + nm + i];
-        }
-#pragma unroll
-        for (int v = 0; v < LB; ++v) {
-          const int e = e0 + v * nthreads();
-          if (e >= BX * BY) continue;
-          const int bx = e % BX, by = e / BX;
-          const int q = (by >> 1) * CBX + (bx >> 1);
-          const Cx<T> vx = edge_prolong_combine<T>(Cx<T>{cl[q], cl[CB + q]}, Cx<T>{cl[q + CBX], cl[CB + q + CBX]},
-                                                   (by & 1) != 0);
-          const Cx<T> vy = edge_prolong_combine<T>(Cx<T>{cl[2 * CB + q], cl[3 * CB + q]},
-                                                   Cx<T>{cl[2 * CB + q + 1], cl[3 * CB + q + 1]}, (bx & 1) != 0);
-          const int k = S::at(bx, by);
-          pl[k] = u[v][0] + vx.re;
-          pl[S::N + k] = u[v][1] + vx.im;
-          pl[2 * S::N + k] = u[v][2] + vy.re;
-          pl[3 * S::N + k] = u[v][3] + vy.im;
-        }
-      }
-    } else {
-      for (int e = tid; e < BX * BY; e += nthreads()) {
-        const int bx = e % BX, by = e / BX;
-        const int c1 = cx ? wrapm(ox + bx, n) : ox + bx, c2 = cy ? wrapm(oy + by, m) : oy + by;
-        const int64_t i = (int64_t)c2 * n + c1;
-        const int k = S::at(bx, by);
-        if constexpr (PRO) {   // as the prolongation kernel: x + Pr xc
-          const Cx<T> vx = edge_prolong_xy<T>(cc, fz.gc, 0, c1, c2, p);
-          const Cx<T> vy = edge_prolong_xy<T>(cc, fz.gc, 1, c1, c2, p);
-          pl[k] = xc[i] + vx.re;
-          pl[S::N + k] = xc[N + i] + vx.im;
-          pl[2 * S::N + k] = xc[nm + i] + vy.re;
-          pl[3 * S::N + k] = xc[N + nm + i] + vy.im;
-        } else {
-          pl[k] = xc[i];
-          pl[S::N + k] = xc[N + i];
-          pl[2 * S::N + k] = xc[nm + i];
-          pl[3 * S::N + k] = xc[N + nm + i];
-        }
-      }
-    }
-  }
-  __syncthreads();
-  const T mu = (T)mus[tr.slot];
-  constexpr int EA = RES ? 2 : 0, EB = RES ? 1 : 0;   // exact margin the residual window needs
-  if (!cx && !cy)
-    edge_passes<T, BX, BY, BWD, false, false, LO, TX, TY, EA, EB>(pl, bc, a, tr.slot, ox, oy, n, m, N, nm, mu, p);
-  else if (!cy)
-    edge_passes<T, BX, BY, BWD, true, false, LO, TX, TY, EA, EB>(pl, bc, a, tr.slot, ox, oy, n, m, N, nm, mu, p);
-  else if (!cx)
-    edge_passes<T, BX, BY, BWD, false, true, LO, TX, TY, EA, EB>(pl, bc, a, tr.slot, ox, oy, n, m, N, nm, mu, p);
-  else
-    edge_passes<T, BX, BY, BWD, true, true, LO, TX, TY, EA, EB>(pl, bc, a, tr.slot, ox, oy, n, m, N, nm, mu, p);
-  for (int e = tid; e < TX * TY; e += nthreads()) {
-    const int ix = e % TX, iy = e / TX;
-    const int c1 = tr.t0x + ix, c2 = tr.t0y + iy;
-    if (c1 >= n || c2 >= m) continue;
-    const int k = S::at(ix + LO, iy + LO);
-    const int64_t i = (int64_t)c2 * n + c1;
-    xo[i] = pl[k];
-    xo[N + i] = pl[S::N + k];
-    xo[nm + i] = pl[2 * S::N + k];
-    xo[N + nm + i] = pl[3 * S::N + k];
-  }
-  if constexpr (RES) {
-    T* bco = colp(fz.bc, sj, fz.gc.ne);
-    if (!cx && !cy)
-      edge_restrict_tile<T, BX, BY, false, false, LO, TX, TY>(pl, rl, bc, bco, a, tr.slot, ox, oy, tr.t0x, tr.t0y, n,
-                                                             m, N, nm, mu, fz.gc, p);
-    else if (!cy)
-      edge_restrict_tile<T, BX, BY, true, false, LO, TX, TY>(pl, rl, bc, bco, a, tr.slot, ox, oy, tr.t0x, tr.t0y, n,
-                                                            m, N, nm, mu, fz.gc, p);
-    else if (!cx)
-      edge_restrict_tile<T, BX, BY, false, true, LO, TX, TY>(pl, rl, bc, bco, a, tr.slot, ox, oy, tr.t0x, tr.t0y, n,
-                                                            m, N, nm, mu, fz.gc, p);
-    else
-      edge_restrict_tile<T, BX, BY, true, true, LO, TX, TY>(pl, rl, bc, bco, a, tr.slot, ox, oy, tr.t0x, tr.t0y, n,
-                                                           m, N, nm, mu, fz.gc, p);
-  }
-}
-
-// ---- nodal sweeps ---------------------------------------------------------------------------
-// A thread owns one 2 x 2 block of the box's nodes (blocks of HX a row, so that block t is entry t of
-// every parity sub-grid) in all passes: its addresses, its seam flags and its right-hand side are
-// worked out and loaded once, with the iterate, and a pass is LDS reads at constant offsets and
-// arithmetic.  Passes that dealt out a colour's nodes anew each time were bound by the vector units:
-// 230 to 330 instructions per node, three quarters of them addressing and reloading; this form takes
-// 160 to 240.  A sweep from zero (84 % of the vector issue) leaves out what is still zero; the
-// prolongating ones wait for memory half the time.  1024 x 1024 FP32, 48 columns, finest level:
-// restricting sweep 295 us, prolongating with residual 484, prolongating onto the base 416, against
-// 395, 624 and 486; 256 x 256 FP64: 73 and 48 us for the last two, against 103 and 84.
-constexpr int kNodalTile = 32, kNodalThreads = 512;
-
-// The values around a node of block t in the iterate's planes; colours from FIRST on are still zero.
-template <typename T, typename S, int PX, int PY, bool CX, bool CY, int FIRST = 4>
-struct BlockNodes {
-  const T* pl;   // at entry t
-  Seam<CX, CY> sm;
-  const Ph<T>& p;
-  __device__ __forceinline__ Cx<T> get(int d1, int d2) const {
-    const int sx = (PX + d1) & 1, sy = (PY + d2) & 1;
-    if (sx + 2 * sy >= FIRST) return {0, 0};
-    const T* q = pl + (sx + 2 * sy) * S::SUB + ((PY + d2) >> 1) * S::HX + ((PX + d1) >> 1);
-    return phased<CX, CY, T>(Cx<T>{q[0], q[S::N]}, d1, d2, sm, p);
-  }
-};
-
-template <typename T, bool BWD, int MODE>
-struct NodalShape {
-  static constexpr bool RES = (MODE & kRestrict) != 0, PRO = (MODE & kProlong) != 0, BAS = (MODE & kBase) != 0;
-  static constexpr bool TRES = (MODE & kResid) != 0, ZERO = (MODE & kZero) != 0;
-  static constexpr int TX = kNodalTile, LO = RES ? kLoR : kLo;
-  static constexpr int HI = TRES ? kHiN + 1 : kHiN;   // (the tile residual: exact one node above / right too)
-  static constexpr int BX = TX + LO + HI;
-  using S = Split<BX, BX>;
-  // coarse nodes under the box: fine box position b lies over coarse box position b >> 1 and its
-  // neighbours one up
-  static constexpr int CBX = (BX - 1) / 2 + 2, CB = CBX * CBX;
-  // exact margin the residual window (restriction) or the tile residual needs
-  static constexpr int EA = RES ? 2 : (TRES ? 1 : 0), EB = (RES || TRES) ? 1 : 0;
-  static constexpr SweepRects R = sweep_rects(false, BX, BX, LO, TX, TX, EA, EB, BWD);
-  static_assert(R.ok, "the halo does not cover the sweep's dependency cone");
-  static_assert(S::SUB <= kNodalThreads && CB <= kNodalThreads, "a block per thread");
-};
+// ---- edge sweeps ----------------------------------------------------------------------------
+// XXHEAD
+constexpr int kTile = 32, kThreads = 512;
 
 // The values of a block's four nodes in a column, colour by colour: off is the byte offset of its
 // first node in a plane, row that of a row; wide: two neighbouring values in one load.
@@ -569,6 +218,318 @@ __device__ __forceinline__ void load_block(const T* c, int64_t N, unsigned off, 
   }
 }
 
+// Runs f(integral_constant<int, 0 .. 3>).
+template <typename F>
+__device__ __forceinline__ void four(const F& f) {
+  f(std::integral_constant<int, 0>{});
+  f(std::integral_constant<int, 1>{});
+  f(std::integral_constant<int, 2>{});
+  f(std::integral_constant<int, 3>{});
+}
+
+// The edges around a node of block t in the iterate's planes (x-edge re, x-edge im, y-edge re, y-edge
+// im).  FROM0: forward passes of a sweep from zero before which nothing is stored: none (4: all is);
+// the edges that no pass before PASS has written are zero (x-edges of odd rows before pass 2, y-edges
+// of odd columns before pass 1, all of them in pass 0).
+template <typename T, typename S, int PX, int PY, bool CX, bool CY, int PASS = 4>
+struct BlockEdges {
+  T* pl;   // at entry t
+  Seam<CX, CY> sm;
+  const Ph<T>& p;
+  static constexpr bool unset(int c, int d1, int d2) {
+    return c == 0 ? PASS == 0 || (PASS <= 2 && ((PY + d2) & 1)) : PASS == 0 || (PASS <= 1 && ((PX + d1) & 1));
+  }
+  __device__ __forceinline__ T* at(int c, int d1, int d2) const {
+    const int sx = (PX + d1) & 1, sy = (PY + d2) & 1;
+    return pl + c * 2 * S::N + (sx + 2 * sy) * S::SUB + ((PY + d2) >> 1) * S::HX + ((PX + d1) >> 1);
+  }
+  __device__ __forceinline__ Cx<T> get(int c, int d1, int d2) const {
+    if (unset(c, d1, d2)) return {0, 0};
+    const T* q = at(c, d1, d2);
+    return phased<CX, CY, T>(Cx<T>{q[0], q[S::N]}, d1, d2, sm, p);
+  }
+  // as add_ext(): a value written one period back is stored times alpha (beta)
+  __device__ __forceinline__ void add(int c, int d1, int d2, Cx<T> v) const {
+    if (CX && d1 < 0) v = pick(sm.lx, cmul(v, p.ar, p.ai), v);
+    if (CY && d2 < 0) v = pick(sm.ly, cmul(v, p.br, p.bi), v);
+    T* q = at(c, d1, d2);
+    q[0] = (unset(c, d1, d2) ? (T)0 : q[0]) + v.re;
+    q[S::N] = (unset(c, d1, d2) ? (T)0 : q[S::N]) + v.im;
+  }
+};
+// The right-hand side on a patch's edges: x (0, 0), x (-1, 0), y (0, 0), y (0, -1).
+template <typename T>
+struct PatchRhs {
+  Cx<T> q[4];
+  __device__ __forceinline__ Cx<T> get(int c, int d1, int d2) const { return q[2 * c + (d1 < 0 || d2 < 0 ? 1 : 0)]; }
+};
+
+template <typename T, bool BWD, int MODE>
+struct EdgeShape {
+  static constexpr bool RES = (MODE & kRestrict) != 0, PRO = (MODE & kProlong) != 0, ZERO = (MODE & kZero) != 0;
+  static constexpr int TX = kTile, LO = RES ? kLoR : kLo, BX = TX + LO + (RES ? kHiER : kHiE);
+  using S = Split<BX, BX>;
+  static constexpr int EA = RES ? 2 : 0, EB = RES ? 1 : 0;   // exact margin the residual window needs
+  static constexpr SweepRects R = sweep_rects(true, BX, BX, LO, TX, TX, EA, EB, BWD);
+  static_assert(R.ok, "the halo does not cover the sweep's dependency cone");
+  static_assert(S::SUB <= kThreads, "a block per thread");
+};
+
+template <typename T, bool BWD, int MODE, bool CX, bool CY>
+__device__ __forceinline__ void edge_tile(T* pl, const T* xc, T* xo, const T* bc, const T* cc, T* bco, const EdgeArgs& e,
+                                          int slot, int t0x, int t0y, int n, int m, int64_t N, int64_t nm, const Geo& gc,
+                                          T mu, const Ph<T>& p, bool wide) {
+  using H = EdgeShape<T, BWD, MODE>;
+  using S = typename H::S;
+  struct alignas(2 * sizeof(T)) Pair {
+    T a, b;
+  };
+  // FP32 keeps the block's right-hand side and loads a pass's patch inverse one pass ahead; in FP64
+  // the registers that this takes would halve the waves
+  constexpr bool AHEAD = sizeof(T) == 4;
+  constexpr int LO = H::LO, BX = H::BX, TX = H::TX;
+  constexpr SweepRects R = H::R;
+  const int tid = (int)threadIdx.x;
+  const bool live = tid < S::SUB;
+  const int t = live ? tid : 0, a = t % S::HX, b = t / S::HX;
+  const int ox = t0x - LO, oy = t0y - LO;   // canonical node of box position 0 (unwrapped)
+  // canonical first node of the block (n, m, ox and oy are even: a block never straddles the seam,
+  // and where the box has an odd number of nodes its last block still lies in the grid)
+  const int p1 = CX ? wrapm(ox + 2 * a, n) : ox + 2 * a, p2 = CY ? wrapm(oy + 2 * b, m) : oy + 2 * b;
+  constexpr unsigned E = (unsigned)sizeof(T);
+  const unsigned off = (unsigned)(p2 * n + p1) * E, row = (unsigned)n * E;
+  // the column left of the block and the row below it, wrapped
+  const unsigned left = CX && p1 == 0 ? off + row - E : off - E, low = CY && p2 == 0 ? (unsigned)((m - 1) * n + p1) * E : off - row;
+  const unsigned corner = CX && p1 == 0 ? low + row - E : low - E;
+  Cx<T> bx[4], by[4], bl[2], bd[2];   // right-hand side: the block's edges, x-edges left, y-edges below
+  auto load_left = [&](int y) {
+    const Cx<T> v{at32(bc, left + y * row), at32(bc + N, left + y * row)};
+    return CX ? pick(p1 == 0, cmul(v, p.ar, -p.ai), v) : v;
+  };
+  auto load_low = [&](int x) {
+    const Cx<T> v{at32(bc + nm, low + x * E), at32(bc + N + nm, low + x * E)};
+    return CY ? pick(p2 == 0, cmul(v, p.br, -p.bi), v) : v;
+  };
+  auto load_own = [&](int comp, int c) {
+    const T* q = comp ? bc + nm : bc;
+    const unsigned o = off + (c >> 1) * row + (c & 1) * E;
+    return Cx<T>{at32(q, o), at32(q + N, o)};
+  };
+  if constexpr (AHEAD) {
+    load_block(bc, N, off, row, wide, bx);
+    load_block(bc + nm, N, off, row, wide, by);
+    for (int k = 0; k < 2; ++k) {
+      bl[k] = load_left(k);
+      bd[k] = load_low(k);
+    }
+  }
+  // kappa of the 3 x 3 cells around the block, from the one below and left of it
+  const T* kp = pick_si<T>(e.k64, e.k32);
+  kp += (int64_t)slot * nm;
+  const T kap9[3][3] = {{at32(kp, corner), at32(kp, low), at32(kp, low + E)},
+                        {at32(kp, left), at32(kp, off), at32(kp, off + E)},
+                        {at32(kp, left + row), at32(kp, off + row), at32(kp, off + row + E)}};
+  const T* wp = pick_si<T>(e.si64, e.si32) + kPatchW * ((int64_t)slot * nm + (int64_t)p2 * n + p1);
+  T w[2][kPatchW];
+  auto load_w = [&](int c, T (&v)[kPatchW]) {
+    const Pair* q = reinterpret_cast<const Pair*>(wp + kPatchW * ((int64_t)(c >> 1) * n + (c & 1)));
+#pragma unroll
+    for (int k = 0; k < kPatchW / 2; ++k) {
+      const Pair u = q[k];
+      v[2 * k] = u.a;
+      v[2 * k + 1] = u.b;
+    }
+  };
+  if constexpr (AHEAD) load_w(BWD ? 3 : 0, w[0]);
+  T* pt = pl + t;
+  if constexpr (!H::ZERO) {
+    Cx<T> ux[4], uy[4];
+    load_block(xc, N, off, row, wide, ux);
+    load_block(xc + nm, N, off, row, wide, uy);
+    if constexpr (H::PRO) {   // as the prolongation kernel: x + Pr xc
+      // a coarse value across the period takes its phase as fetch() has it
+      const bool xh = p1 == n - 2, yh = p2 == m - 2;
+      const unsigned j = (unsigned)((p2 >> 1) * gc.n + (p1 >> 1)) * E;
+      const unsigned jx = xh ? j + E - (unsigned)gc.n * E : j + E, jy = yh ? (unsigned)(p1 >> 1) * E : j + (unsigned)gc.n * E;
+      const T *cx = cc, *cy = cc + gc.nm;
+      const Cx<T> x00{at32(cx, j), at32(cx + gc.ne, j)}, y00{at32(cy, j), at32(cy + gc.ne, j)};
+      Cx<T> x01{at32(cx, jy), at32(cx + gc.ne, jy)}, y10{at32(cy, jx), at32(cy + gc.ne, jx)};
+      if (yh) x01 = cmul(x01, p.br, p.bi);
+      if (xh) y10 = cmul(y10, p.ar, p.ai);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        ux[c] = ux[c] + edge_prolong_combine<T>(x00, x01, c >> 1);
+        uy[c] = uy[c] + edge_prolong_combine<T>(y00, y10, c & 1);
+      }
+    }
+    if (live)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        pt[c * S::SUB] = ux[c].re;
+        pt[S::N + c * S::SUB] = ux[c].im;
+        pt[2 * S::N + c * S::SUB] = uy[c].re;
+        pt[3 * S::N + c * S::SUB] = uy[c].im;
+      }
+    __syncthreads();
+  }
+  const T s = (T)e.s, mx = (T)e.mx, my = (T)e.my, mmx = mu * mx, mmy = mu * my;
+  four([&](auto order) {
+    constexpr int k = decltype(order)::value, c = BWD ? 3 - k : k, px = c & 1, py = c >> 1;
+    constexpr PassRect r = R.r[k];
+    static_assert((r.x0 & 1) == px && (r.y0 & 1) == py && r.x0 >= 1 && r.y0 >= 1 && r.x1 <= BX - 2 && r.y1 <= BX - 2,
+                  "pass rectangle");
+    if constexpr (AHEAD && k < 3) load_w(BWD ? 2 - k : k + 1, w[(k + 1) & 1]);
+    if (live && a >= (r.x0 >> 1) && a <= (r.x1 >> 1) && b >= (r.y0 >> 1) && b <= (r.y1 >> 1)) {
+      PatchRhs<T> rhs;
+      if constexpr (AHEAD) {
+        rhs.q[0] = bx[c];
+        rhs.q[1] = px ? bx[c & 2] : bl[py];
+        rhs.q[2] = by[c];
+        rhs.q[3] = py ? by[c & 1] : bd[px];
+      } else {
+        load_w(c, w[k & 1]);
+        rhs.q[0] = load_own(0, c);
+        rhs.q[1] = px ? load_own(0, c & 2) : load_left(py);
+        rhs.q[2] = load_own(1, c);
+        rhs.q[3] = py ? load_own(1, c & 1) : load_low(px);
+      }
+      const BlockEdges<T, S, px, py, CX, CY, H::ZERO ? k : 4> x{pt, Seam<CX, CY>(p1 + px, p2 + py, n, m), p};
+      if constexpr (H::ZERO && k == 0)
+        patch_solve<T>(x, w[k & 1], rhs.q[0], rhs.q[1], rhs.q[2], rhs.q[3]);
+      else
+        patch_update<T>(x, rhs, kap9[py + 1][px + 1], kap9[py + 1][px], kap9[py][px], kap9[py][px + 1], w[k & 1], s, mmx, mmy);
+    }
+    __syncthreads();
+  });
+  // the tile, whole rows at a time
+  constexpr int ROWS = kThreads / TX, RK = TX / ROWS;
+  const int ix = tid % TX, iy = tid / TX;
+#pragma unroll
+  for (int k = 0; k < RK; ++k) {
+    const int c1 = t0x + ix, c2 = t0y + iy + k * ROWS;
+    if (c1 >= n || c2 >= m) continue;
+    const T* q = pl + S::at(ix + LO, iy + k * ROWS + LO);
+    const unsigned i = (unsigned)(c2 * n + c1) * E;
+    at32(xo, i) = q[0];
+    at32(xo + N, i) = q[S::N];
+    at32(xo + nm, i) = q[2 * S::N];
+    at32(xo + N + nm, i) = q[3 * S::N];
+  }
+  if constexpr (H::RES) {
+    // the residual b - (A + mu M) x (as the residual kernel computes it) in the window from one node
+    // below and left of the tile that the restriction to the tile's coarse edges reads
+    constexpr int W0 = LO - 1, W1 = LO + TX - 1;
+    Cx<T> rx[4], ry[4];
+    four([&](auto colour) {
+      constexpr int c = decltype(colour)::value, px = c & 1, py = c >> 1;
+      const int qx = 2 * a + px, qy = 2 * b + py;
+      rx[c] = ry[c] = {0, 0};
+      if (live && qx >= W0 && qx <= W1 && qy >= W0 && qy <= W1) {
+        const BlockEdges<T, S, px, py, CX, CY> x{pt, Seam<CX, CY>(p1 + px, p2 + py, n, m), p};
+        const Cx<T> ox0 = AHEAD ? bx[c] : load_own(0, c), oy0 = AHEAD ? by[c] : load_own(1, c);
+        Cx<T> Au, Mu;
+        edge_AM_acc<T>(x, 0, kap9[py][px + 1], kap9[py + 1][px + 1], s, mx, Au, Mu);
+        rx[c] = ox0 - (Au + (mu * Mu));
+        edge_AM_acc<T>(x, 1, kap9[py + 1][px + 1], kap9[py + 1][px], s, my, Au, Mu);
+        ry[c] = oy0 - (Au + (mu * Mu));
+      }
+    });
+    __syncthreads();   // the iterate has been read: its planes take the residual
+    if (live)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        pt[c * S::SUB] = rx[c].re;
+        pt[S::N + c * S::SUB] = rx[c].im;
+        pt[2 * S::N + c * S::SUB] = ry[c].re;
+        pt[3 * S::N + c * S::SUB] = ry[c].im;
+      }
+    __syncthreads();
+    const int f1 = ox + 2 * a, f2 = oy + 2 * b;
+    if (live && a >= LO / 2 && a < (LO + TX) / 2 && b >= LO / 2 && b < (LO + TX) / 2 && f1 < n && f2 < m) {
+      const BlockEdges<T, S, 0, 0, CX, CY> r{pt, Seam<CX, CY>(p1, p2, n, m), p};
+      const Cx<T> vx = edge_restrict_acc<T>(r, 0), vy = edge_restrict_acc<T>(r, 1);
+      const unsigned J = (unsigned)((f2 >> 1) * gc.n + (f1 >> 1)) * E;
+      at32(bco, J) = vx.re;
+      at32(bco + gc.ne, J) = vx.im;
+      at32(bco + gc.nm, J) = vy.re;
+      at32(bco + gc.ne + gc.nm, J) = vy.im;
+    }
+  }
+}
+
+template <typename T, bool BWD, int MODE>
+__global__ __launch_bounds__(kThreads) void k_edge_sweep(View<const T> xin, View<T> xout, View<const T> bv, EdgeArgs a, Geo g,
+                                                      const Phase* __restrict__ phs, const double* __restrict__ mus,
+                                                      int wide, const int* __restrict__ slots, int ncps, int tiles_x,
+                                                      SweepFuse<T> fz) {
+  static_assert(!((MODE & (kRestrict | kZero)) && BWD), "the order of the colours");
+  static_assert(!(MODE & (kBase | kResid)), "nodal sweeps only");
+  using H = EdgeShape<T, BWD, MODE>;
+  __shared__ T pl[4 * H::S::N];
+  const TileRef tr = tile_ref(slots, ncps, tiles_x, H::TX, H::TX);
+  const int n = g.n, m = g.m;
+  const int64_t N = g.ne, nm = g.nm;
+  const int ox = tr.t0x - H::LO, oy = tr.t0y - H::LO;
+  const bool cx = !(ox >= 0 && ox + H::BX <= n), cy = !(oy >= 0 && oy + H::BX <= m);
+  const SJ sj{tr.slot, tr.j};
+  T* xo = colp(xout, sj, N);
+  const T* bc = colp(bv, sj, N);
+  const T* xc = H::ZERO ? nullptr : colp(xin, sj, N);
+  const T* cc = H::PRO ? colp(fz.xc, sj, fz.gc.ne) : nullptr;
+  T* bco = H::RES ? colp(fz.bc, sj, fz.gc.ne) : nullptr;
+  const Ph<T> p = cast_phase<T>(phs[tr.slot]);
+  const T mu = (T)mus[tr.slot];
+#define BL_TILE(CX, CY) \
+  edge_tile<T, BWD, MODE, CX, CY>(pl, xc, xo, bc, cc, bco, a, tr.slot, tr.t0x, tr.t0y, n, m, N, nm, fz.gc, mu, p, wide != 0)
+  if (!cx && !cy) BL_TILE(false, false);
+  else if (!cy) BL_TILE(true, false);
+  else if (!cx) BL_TILE(false, true);
+  else BL_TILE(true, true);
+#undef BL_TILE
+}
+
+// ---- nodal sweeps ---------------------------------------------------------------------------
+// A thread owns one 2 x 2 block of the box's nodes (blocks of HX a row, so that block t is entry t of
+// every parity sub-grid) in all passes: its addresses, its seam flags and its right-hand side are
+// worked out and loaded once, with the iterate, and a pass is LDS reads at constant offsets and
+// arithmetic.  Passes that dealt out a colour's nodes anew each time were bound by the vector units:
+// 230 to 330 instructions per node, three quarters of them addressing and reloading; this form takes
+// 160 to 240.  A sweep from zero (84 % of the vector issue) leaves out what is still zero; the
+// prolongating ones wait for memory half the time.  1024 x 1024 FP32, 48 columns, finest level:
+// restricting sweep 295 us, prolongating with residual 484, prolongating onto the base 416, against
+// 395, 624 and 486; 256 x 256 FP64: 73 and 48 us for the last two, against 103 and 84.
+// The values around a node of block t in the iterate's planes; colours from FIRST on are still zero.
+template <typename T, typename S, int PX, int PY, bool CX, bool CY, int FIRST = 4>
+struct BlockNodes {
+  const T* pl;   // at entry t
+  Seam<CX, CY> sm;
+  const Ph<T>& p;
+  __device__ __forceinline__ Cx<T> get(int d1, int d2) const {
+    const int sx = (PX + d1) & 1, sy = (PY + d2) & 1;
+    if (sx + 2 * sy >= FIRST) return {0, 0};
+    const T* q = pl + (sx + 2 * sy) * S::SUB + ((PY + d2) >> 1) * S::HX + ((PX + d1) >> 1);
+    return phased<CX, CY, T>(Cx<T>{q[0], q[S::N]}, d1, d2, sm, p);
+  }
+};
+
+template <typename T, bool BWD, int MODE>
+struct NodalShape {
+  static constexpr bool RES = (MODE & kRestrict) != 0, PRO = (MODE & kProlong) != 0, BAS = (MODE & kBase) != 0;
+  static constexpr bool TRES = (MODE & kResid) != 0, ZERO = (MODE & kZero) != 0;
+  static constexpr int TX = kTile, LO = RES ? kLoR : kLo;
+  static constexpr int HI = TRES ? kHiN + 1 : kHiN;   // (the tile residual: exact one node above / right too)
+  static constexpr int BX = TX + LO + HI;
+  using S = Split<BX, BX>;
+  // coarse nodes under the box: fine box position b lies over coarse box position b >> 1 and its
+  // neighbours one up
+  static constexpr int CBX = (BX - 1) / 2 + 2, CB = CBX * CBX;
+  // exact margin the residual window (restriction) or the tile residual needs
+  static constexpr int EA = RES ? 2 : (TRES ? 1 : 0), EB = (RES || TRES) ? 1 : 0;
+  static constexpr SweepRects R = sweep_rects(false, BX, BX, LO, TX, TX, EA, EB, BWD);
+  static_assert(R.ok, "the halo does not cover the sweep's dependency cone");
+  static_assert(S::SUB <= kThreads && CB <= kThreads, "a block per thread");
+};
+
 template <typename T, bool BWD, int MODE, bool CX, bool CY>
 __device__ __forceinline__ void nodal_tile(T* pl, T* cl, const T* xc, T* xo, const T* bc, const T* cc, T* bco, const T* bs,
                                            T* ro, const NodalStencil& st, int t0x, int t0y, int n, int m, int64_t N,
@@ -589,7 +550,7 @@ __device__ __forceinline__ void nodal_tile(T* pl, T* cl, const T* xc, T* xo, con
   load_block(bc, N, off, row, wide, rhs);
   if constexpr (!H::ZERO) load_block(xc, N, off, row, wide, u);
   // the tile, whole rows at a time
-  constexpr int ROWS = kNodalThreads / TX, RK = TX / ROWS;
+  constexpr int ROWS = kThreads / TX, RK = TX / ROWS;
   const int ix = tid % TX, iy = tid / TX;
   Cx<T> base[RK];
   if constexpr (H::BAS)
@@ -713,7 +674,7 @@ __device__ __forceinline__ void nodal_tile(T* pl, T* cl, const T* xc, T* xo, con
 }
 
 template <typename T, bool BWD, int MODE>
-__global__ __launch_bounds__(kNodalThreads) void k_nodal_sweep(View<const T> xin, View<T> xout, View<const T> bv, Geo g,
+__global__ __launch_bounds__(kThreads) void k_nodal_sweep(View<const T> xin, View<T> xout, View<const T> bv, Geo g,
                                                             const Phase* __restrict__ phs, NodalStencil st,
                                                             int wide, const int* __restrict__ slots, int ncps,
                                                             int tiles_x, SweepFuse<T> fz) {
@@ -747,65 +708,48 @@ __global__ __launch_bounds__(kNodalThreads) void k_nodal_sweep(View<const T> xin
     nodal_tile<T, BWD, MODE, true, true>(pl, cl, xc, xo, bc, cc, bco, bs, ro, st, tr.t0x, tr.t0y, n, m, N, fz.gc, p, wide != 0);
 }
 
-// Edge tile shapes (nodes): 0: 32 x 32, 1: 64 x 32 (FP32; the FP64 box exceeds the static LDS limit).
-// 512 threads when the launch has fewer than four tile workgroups per compute unit
-inline unsigned sweep_threads(const dim3& grid) { return (uint64_t)grid.x * grid.y < 1024 ? 512u : 256u; }
-
-template <typename T, int TX, int TY, bool BWD, int MODE>
-void edge_go(View<const T> xin, View<T> xout, View<const T> b, const EdgeArgs& a, const Geo& g, const Phase* ph,
-             const double* mu, bool zero_start, const SweepFuse<T>& fz, const Launch& L) {
-  const int tx = (g.n + TX - 1) / TX, ty = (g.m + TY - 1) / TY;
-  dim3 grid((unsigned)(tx * ty), (unsigned)(L.nact * L.ncps));
-  // the restricting sweep's LDS (box and residual window) admits three workgroups per compute
-  // unit: 512 threads each keep the occupancy up
-  k_edge_sweep<T, TX, TY, BWD, MODE><<<grid, (MODE & kRestrict) ? 512u : sweep_threads(grid), 0, L.st>>>(xin, xout, b, a, g, ph, mu, zero_start ? 1 : 0,
-                                                                  L.slots, L.ncps, tx, fz);
+// Two values a load where the columns (whole numbers of pairs) start on a pair.
+template <typename T>
+int wide_loads(View<const T> b, View<const T> x) {
+  return (((uintptr_t)b.p | (uintptr_t)x.p) & (2 * sizeof(T) - 1)) == 0 ? 1 : 0;
 }
 
-template <typename T, int TX, int TY>
-void edge_launch(View<const T> xin, View<T> xout, View<const T> b, const EdgeArgs& a, const Geo& g, const Phase* ph,
-                 const double* mu, bool backward, bool zero_start, const SweepFuse<T>& fz, const Launch& L) {
-  if (backward) {
-    if (fz.xc.p) edge_go<T, TX, TY, true, kProlong>(xin, xout, b, a, g, ph, mu, zero_start, fz, L);
-    else edge_go<T, TX, TY, true, 0>(xin, xout, b, a, g, ph, mu, zero_start, fz, L);
-    return;
-  }
-  if constexpr (sizeof(T) == 4 && TX * TY <= 1024) {   // the residual window fits LDS: FP32, 32 x 32
-    if (fz.bc.p) {
-      edge_go<T, TX, TY, false, kRestrict>(xin, xout, b, a, g, ph, mu, zero_start, fz, L);
-      return;
-    }
-  }
-  edge_go<T, TX, TY, false, 0>(xin, xout, b, a, g, ph, mu, zero_start, fz, L);
+template <typename T, bool BWD, int MODE>
+void edge_go(View<const T> xin, View<T> xout, View<const T> b, const EdgeArgs& a, const Geo& g, const Phase* ph,
+             const double* mu, const SweepFuse<T>& fz, const Launch& L) {
+  const int tx = (g.n + kTile - 1) / kTile, ty = (g.m + kTile - 1) / kTile;
+  dim3 grid((unsigned)(tx * ty), (unsigned)(L.nact * L.ncps));
+  k_edge_sweep<T, BWD, MODE><<<grid, kThreads, 0, L.st>>>(xin, xout, b, a, g, ph, mu, wide_loads(b, xin), L.slots, L.ncps, tx,
+                                                         fz);
 }
 
 template <typename T, bool BWD, int MODE>
 void nodal_go(View<const T> xin, View<T> xout, View<const T> b, const Geo& g, const Phase* ph, const NodalStencil& c,
               const SweepFuse<T>& fz, const Launch& L) {
-  const int tx = (g.n + kNodalTile - 1) / kNodalTile, ty = (g.m + kNodalTile - 1) / kNodalTile;
+  const int tx = (g.n + kTile - 1) / kTile, ty = (g.m + kTile - 1) / kTile;
   dim3 grid((unsigned)(tx * ty), (unsigned)(L.nact * L.ncps));
-  // two values a load where the columns (whole numbers of pairs) start on a pair
-  const bool wide = (((uintptr_t)b.p | (uintptr_t)xin.p) & (2 * sizeof(T) - 1)) == 0;
-  k_nodal_sweep<T, BWD, MODE><<<grid, kNodalThreads, 0, L.st>>>(xin, xout, b, g, ph, c, wide ? 1 : 0, L.slots, L.ncps, tx, fz);
+  k_nodal_sweep<T, BWD, MODE><<<grid, kThreads, 0, L.st>>>(xin, xout, b, g, ph, c, wide_loads(b, xin), L.slots, L.ncps, tx,
+                                                          fz);
 }
 
 }  // namespace
 
-bool edge_sweep_restricts(size_t elem) { return elem == 4; }
-
 template <typename T>
 void edge_sweep(View<const T> xin, View<T> xout, View<const T> b, const double* kappa64, const float* kappa32,
                 const double* sinv64, const float* sinv32, const Geo& g, const Phase* ph, const double* mu,
-                const PatchT& T4, bool backward, bool zero_start, int tile, const Launch& L, const SweepFuse<T>& fz) {
+                bool backward, bool zero_start, const Launch& L, const SweepFuse<T>& fz) {
   if (L.nact * L.ncps == 0) return;
-  const EdgeArgs a{kappa64, kappa32, sinv64, sinv32, T4, g.s, g.mx, g.my};
-  if constexpr (sizeof(T) == 4) {
-    if (tile == 1 && !fz.bc.p) {
-      edge_launch<T, 64, 32>(xin, xout, b, a, g, ph, mu, backward, zero_start, fz, L);
-      return;
-    }
+  const EdgeArgs a{kappa64, kappa32, sinv64, sinv32, g.s, g.mx, g.my};
+  if (backward) {
+    if (fz.xc.p) edge_go<T, true, kProlong>(xin, xout, b, a, g, ph, mu, fz, L);
+    else edge_go<T, true, 0>(xin, xout, b, a, g, ph, mu, fz, L);
+  } else if (fz.bc.p) {
+    if (zero_start) edge_go<T, false, kRestrict | kZero>(xin, xout, b, a, g, ph, mu, fz, L);
+    else edge_go<T, false, kRestrict>(xin, xout, b, a, g, ph, mu, fz, L);
+  } else {
+    if (zero_start) edge_go<T, false, kZero>(xin, xout, b, a, g, ph, mu, fz, L);
+    else edge_go<T, false, 0>(xin, xout, b, a, g, ph, mu, fz, L);
   }
-  edge_launch<T, 32, 32>(xin, xout, b, a, g, ph, mu, backward, zero_start, fz, L);
 }
 
 template <typename T>
@@ -831,8 +775,8 @@ void nodal_sweep(View<const T> xin, View<T> xout, View<const T> b, const Geo& g,
   }
 }
 
-template void edge_sweep<double>(View<const double>, View<double>, View<const double>, const double*, const float*, const double*, const float*, const Geo&, const Phase*, const double*, const PatchT&, bool, bool, int, const Launch&, const SweepFuse<double>&);
-template void edge_sweep<float>(View<const float>, View<float>, View<const float>, const double*, const float*, const double*, const float*, const Geo&, const Phase*, const double*, const PatchT&, bool, bool, int, const Launch&, const SweepFuse<float>&);
+template void edge_sweep<double>(View<const double>, View<double>, View<const double>, const double*, const float*, const double*, const float*, const Geo&, const Phase*, const double*, bool, bool, const Launch&, const SweepFuse<double>&);
+template void edge_sweep<float>(View<const float>, View<float>, View<const float>, const double*, const float*, const double*, const float*, const Geo&, const Phase*, const double*, bool, bool, const Launch&, const SweepFuse<float>&);
 template void nodal_sweep<double>(View<const double>, View<double>, View<const double>, const Geo&, const Phase*, const NodalStencil&, bool, bool, const Launch&, const SweepFuse<double>&);
 template void nodal_sweep<float>(View<const float>, View<float>, View<const float>, const Geo&, const Phase*, const NodalStencil&, bool, bool, const Launch&, const SweepFuse<float>&);
 

@@ -128,13 +128,8 @@ Choice tune_t(bl_solver* s, hipEvent_t e0, hipEvent_t e1) {
 }  // namespace
 
 int engine_autotune(bl_solver* s) {
-  // measurement and test hooks: BL_SWEEP_TILE (edge sweeps: 0 = 32 x 32, 1 = 64 x 32 tiles),
-  // BL_SMOOTH_SHAPE="threads,columns,xcd" and BL_RR_TILE=48|64
+  // measurement and test hooks: BL_SMOOTH_SHAPE="threads,columns,xcd" and BL_RR_TILE=48|64
   // fix the shapes instead of timing them
-  if (const char* e = std::getenv("BL_SWEEP_TILE")) {
-    int a = 0;
-    if (std::sscanf(e, "%d", &a) == 1 && a >= 0 && a < 2) s->tune_sweep = a;
-  }
   const char* fs = std::getenv("BL_SMOOTH_SHAPE");
   const char* ft = std::getenv("BL_RR_TILE");
   if (fs || ft) {
