@@ -233,6 +233,7 @@ struct CoarseCycle {
   int xo[kMaxFused];    // LDS offsets (elements): iterate and right-hand side per level, and the
   int bo[kMaxFused];    // residual; groups of 64 rows that the dense solve takes at a time (set by
   int ro, groups;       // the launch)
+  int cycles;           // nodal cycles: their number, each after the first on the residual
   NodalStencil ns;      // nodal cycles
   CoarseLevel L[kMaxFused];
 };

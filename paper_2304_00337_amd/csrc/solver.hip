@@ -291,6 +291,7 @@ CoarseCycle coarse_cycle(const bl_solver* s, int first, const void* inv, int64_t
   C.nlev = (int)s->lv.size() - first;
   C.nu_pre = s->opts.nu_pre;
   C.nu_post = s->opts.nu_post;
+  C.cycles = 1;
   C.nc = nc;
   C.inv = inv;
   C.ns = s->ns;
@@ -548,6 +549,13 @@ bool vcycle_nodal(bl_solver* s, int l, View<const T> b, View<T> x, const Launch&
 template <typename T>
 void nodal_solve(bl_solver* s, View<const T> b, View<T> phi, const Launch& L, int cycles, int lev = 0) {
   const int pr = PrecOf<T>::v;
+  if (lev == s->fuse_nodal[pr]) {   // residuals and sums stay in the fused cycles' workgroup
+    CoarseCycle C = coarse_cycle(s, lev, pc_inv<T>(s), s->ncn);
+    C.cycles = cycles;
+    nodal_vcycle_fused<T>(b, phi, C, s->ph_d, L);
+    s->launches += 1;
+    return;
+  }
   View<T> res = view(static_cast<T*>(s->nodal_extra[pr][0]), s->nodal_extra_cap[pr]);
   View<T> cor = view(static_cast<T*>(s->nodal_extra[pr][1]), s->nodal_extra_cap[pr]);
   // the first cycle's last sweep also forms the residual the second cycle starts from

@@ -36,3 +36,23 @@ def test_fused_cycles_equal_per_level_cycles(n, m, levels, precision):
     for ref, got in zip(*out):
         assert np.isfinite(ref).all() and np.abs(ref).max() > 0
         assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("n,m", [(20, 12), (32, 32), (4, 4)])
+@pytest.mark.parametrize("cycles", [1, 2, 3])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_fused_nodal_solve_equals_cycles_one_by_one(n, m, cycles, precision):
+    import torch
+
+    from paper_2304_00337_amd.api import Solver, from_device_block, to_device_block
+    eps = np.random.default_rng(n).uniform(1.0, 9.0, n * m)
+    b = np.random.default_rng(m).standard_normal((2 * n * m, 3, 2)) @ [1, 1j]
+    out = []
+    for fuse in (0, 1):
+        with Solver(n, m, 1.0, 0.8, eps, nev=1, nthrow=0, coarsest_min=2, mu=5.0, autotune=0, precision=precision,
+                    coarse_fuse=fuse, nodal_cycles=cycles) as s:
+            s.set_k(0.9, -0.7)
+            assert s.info()["fused_nodal_level"] == (0 if fuse else -1)
+            x = to_device_block(b)
+            out.append(from_device_block(s.apply("PROJECT", x, out=torch.empty_like(x))))
+    assert np.isfinite(out[0]).all() and np.array_equal(out[0], out[1])
