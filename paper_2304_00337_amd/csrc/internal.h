@@ -92,10 +92,12 @@ void pw_tables(const PlaneWave* par, double* tab, int64_t tabstride, int n, int 
 // mode 0: reduce the w^* b partials (count blocks) of every launch column into coef[0..3];
 // mode 1: reduce the w^* phi' partials into coef[4..5] = c - w^* phi' / nm.
 void pw_reduce(const PWDefl& d, int mode, int count, const Launch& L);
-// b -= w (w^* b / nm) on the launch's nodal columns (partial-free).
+// b -= w (w^* b / nm) on the launch's nodal columns; with count > 0 (at most 256) it reduces the
+// w^* b partials itself, as pw_reduce of mode 0.
 template <typename T>
-void pw_rhs(View<T> b, const Geo& g, const PWDefl& d, const Launch& L);
-// partials of w^* phi on the launch's nodal columns; returns the block count.
+void pw_rhs(View<T> b, const Geo& g, const PWDefl& d, int count, const Launch& L);
+// partials of w^* phi on the launch's nodal columns; returns the block count (1: the coefficients
+// are set too, as by pw_reduce of mode 1).
 template <typename T>
 int pw_dot(View<const T> phi, const Geo& g, const PWDefl& d, const Launch& L);
 int pw_blocks(const Geo& g);
