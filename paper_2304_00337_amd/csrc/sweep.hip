@@ -237,9 +237,9 @@ __device__ __forceinline__ void four(const F& f) {
 }
 
 // The edges around a node of block t in the iterate's planes (x-edge re, x-edge im, y-edge re, y-edge
-// im).  FROM0: forward passes of a sweep from zero before which nothing is stored: none (4: all is);
-// the edges that no pass before PASS has written are zero (x-edges of odd rows before pass 2, y-edges
-// of odd columns before pass 1, all of them in pass 0).
+// im).  In pass PASS of a forward sweep from zero (4: everything is stored) the edges that no earlier
+// pass has written are zero: all of them in pass 0, x-edges of odd rows up to pass 2, y-edges of odd
+// columns up to pass 1.
 template <typename T, typename S, int PX, int PY, bool CX, bool CY, int PASS = 4>
 struct BlockEdges {
   T* pl;   // at entry t
