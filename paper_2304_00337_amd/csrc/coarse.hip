@@ -507,12 +507,12 @@ __global__ __launch_bounds__((nodal_threads<T, LP>())) void k_nodal_vcycle_fused
           X.store(0, X.index(j1, j2), v);
         });
       } else {
-        const Plane<T, 2> X(base + C.xo[last], g);
+        const P1 X(base + C.xo[last], g);
 #pragma unroll 1
-        for (int i = tid >> 1; i < nc; i += nt >> 1) {
-          const T v = dense_row<T>(inv, nc, base + C.bo[last], i, tid & 1);
+        for (int i = tid; i < nc; i += nt) {
+          const Cx<T> v = dense_row<T>(inv, nc, base + C.bo[last], i);
           split_index(i, g.n, j1, j2);
-          X.store(0, X.index(j1, j2), Cx<T>{v, 0});
+          X.store(0, X.index(j1, j2), v);
         }
         __syncthreads();
       }

@@ -294,24 +294,29 @@ __global__ __launch_bounds__(256) void k_dense_apply_parts(const T* __restrict__
   if (wave < 2 && i < n)   // real, then imaginary parts
     colp(xv, sj, n)[wave * n + i] = dense_sum([&](int k) { return part[2 * k + wave][lane]; });
 }
-// The same with the terms one after the other, two lanes per row (real and imaginary part).
+// The same with the terms one after the other: 64 rows per workgroup, one per lane.
 template <typename T>
-__global__ __launch_bounds__(256) void k_dense_apply(const T* __restrict__ inv, int n, View<const T> bv, View<T> xv,
-                                                     const int* __restrict__ slots, int ncps) {
+__global__ __launch_bounds__(64) void k_dense_apply(const T* __restrict__ inv, int n, View<const T> bv, View<T> xv,
+                                                    const int* __restrict__ slots, int ncps) {
   const SJ sj = slot_col(slots, ncps);
-  const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x), i = t >> 1, part = t & 1;
+  const int i = (int)(blockIdx.x * 64 + threadIdx.x);
   if (i >= n) return;
-  const T* bc = colp(bv, sj, n);
-  colp(xv, sj, n)[part * n + i] = dense_row<T>(inv + (int64_t)sj.slot * n * n * 2, n, bc, i, part);
+  const Cx<T> v = dense_row<T>(inv + (int64_t)sj.slot * n * n * 2, n, colp(bv, sj, n), i);
+  T* xc = colp(xv, sj, n);
+  xc[i] = v.re;
+  xc[n + i] = v.im;
 }
 template <typename T>
 void dense_apply(const void* inv, int64_t n, bool edge, View<const T> b, View<T> x, const Launch& L) {
-  const bool parts = dense_in_parts<T>(edge);
-  dim3 grid((unsigned)(parts ? (n + 63) / 64 : (2 * n + 255) / 256), (unsigned)(L.nact * L.ncps));
+  const dim3 grid((unsigned)((n + 63) / 64), (unsigned)(L.nact * L.ncps));
   if (grid.y == 0) return;
   const T* m = reinterpret_cast<const T*>(inv);
-  if (parts) k_dense_apply_parts<T><<<grid, 256, 0, L.st>>>(m, (int)n, b, x, L.slots, L.ncps);
-  else k_dense_apply<T><<<grid, 256, 0, L.st>>>(m, (int)n, b, x, L.slots, L.ncps);
+  if constexpr (!dense_in_parts<T>(false))
+    if (!edge) {
+      k_dense_apply<T><<<grid, 64, 0, L.st>>>(m, (int)n, b, x, L.slots, L.ncps);
+      return;
+    }
+  k_dense_apply_parts<T><<<grid, 256, 0, L.st>>>(m, (int)n, b, x, L.slots, L.ncps);
 }
 template void dense_apply<double>(const void*, int64_t, bool, View<const double>, View<double>, const Launch&);
 template void dense_apply<float>(const void*, int64_t, bool, View<const float>, View<float>, const Launch&);
