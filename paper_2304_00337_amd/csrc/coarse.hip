@@ -271,9 +271,11 @@ __device__ __forceinline__ void dense_solve(const T* inv, int n, const T* b, T* 
     for (int t = wave; t < ng * kDenseParts; t += waves) {
       const int k = t % kDenseParts, r = t / kDenseParts * 64 + lane, i = g0 * 64 + r;
       if (i < n) {
-        const Cx<T> v = dense_part<T>(inv, n, b, i, n * k / kDenseParts, n * (k + 1) / kDenseParts);
-        part[(2 * k) * (ng * 64) + r] = v.re;
-        part[(2 * k + 1) * (ng * 64) + r] = v.im;
+        const T* const bc[1] = {b};
+        Cx<T> v[1];
+        dense_part<1>(inv, n, bc, i, n * k / kDenseParts, n * (k + 1) / kDenseParts, v);
+        part[(2 * k) * (ng * 64) + r] = v[0].re;
+        part[(2 * k + 1) * (ng * 64) + r] = v[0].im;
       }
     }
     __syncthreads();

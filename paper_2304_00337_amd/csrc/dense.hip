@@ -273,26 +273,34 @@ void invert_coarse(double* ke, float* ke32, int64_t ne, double* kn, float* kn32,
   k_invert_finish<<<dim3((unsigned)((big * big + 255) / 256), (unsigned)(2 * L.nact)), 256, 0, L.st>>>(me, mn, L.slots);
 }
 
-// x = Inv_s b: 64 rows per workgroup, one per lane; each of the four waves sums two of a row's
-// parts (dense_part), which then combine in LDS.
-template <typename T>
-__global__ __launch_bounds__(256) void k_dense_apply_parts(const T* __restrict__ inv, int n, View<const T> bv, View<T> xv,
-                                                     const int* __restrict__ slots, int ncps) {
-  __shared__ T part[2 * kDenseParts][64];
-  const SJ sj = slot_col(slots, ncps);
-  const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+// x = Inv_s b: 64 rows per workgroup, one per lane, for NC columns; each of the eight waves sums one of a
+// row's parts (dense_part), which then combine in LDS.  Bound by latency, but where the matrix exceeds an
+// XCD's L2 (4 MB) by reading it, the workgroups of the columns being at different places of it: 1800
+// edges FP64, 48 columns 102 us with four columns a workgroup, 349 with one.
+template <typename T, int NC>
+__global__ __launch_bounds__(64 * kDenseParts) void k_dense_apply_parts(const T* __restrict__ inv, int n, View<const T> bv,
+                                                                        View<T> xv, const int* __restrict__ slots, int ncps) {
+  __shared__ T part[NC][2 * kDenseParts][64];
+  const SJ g = slot_col(slots, (ncps + NC - 1) / NC);
+  const int lane = (int)threadIdx.x & 63, k = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int i = (int)blockIdx.x * 64 + lane;
-  inv += (int64_t)sj.slot * n * n * 2;
-  const T* bc = colp(bv, sj, n);
-  if (i < n)
-    for (int k = wave; k < kDenseParts; k += 4) {
-      const Cx<T> v = dense_part<T>(inv, n, bc, i, n * k / kDenseParts, n * (k + 1) / kDenseParts);
-      part[2 * k][lane] = v.re;
-      part[2 * k + 1][lane] = v.im;
+  inv += (int64_t)g.slot * n * n * 2;
+  const T* b[NC];   // (columns past the last: the last one again, not stored)
+#pragma unroll
+  for (int c = 0; c < NC; ++c) b[c] = colp(bv, SJ{g.slot, min(g.j * NC + c, ncps - 1)}, n);
+  if (i < n) {
+    Cx<T> v[NC];
+    dense_part<NC>(inv, n, b, i, n * k / kDenseParts, n * (k + 1) / kDenseParts, v);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      part[c][2 * k][lane] = v[c].re;
+      part[c][2 * k + 1][lane] = v[c].im;
     }
+  }
   __syncthreads();
-  if (wave < 2 && i < n)   // real, then imaginary parts
-    colp(xv, sj, n)[wave * n + i] = dense_sum([&](int k) { return part[2 * k + wave][lane]; });
+  const int c = k >> 1, p = k & 1;   // real, then imaginary parts
+  if (c < NC && g.j * NC + c < ncps && i < n)
+    colp(xv, SJ{g.slot, g.j * NC + c}, n)[p * n + i] = dense_sum([&](int q) { return part[c][2 * q + p][lane]; });
 }
 // The same with the terms one after the other: 64 rows per workgroup, one per lane.
 template <typename T>
@@ -308,15 +316,23 @@ __global__ __launch_bounds__(64) void k_dense_apply(const T* __restrict__ inv, i
 }
 template <typename T>
 void dense_apply(const void* inv, int64_t n, bool edge, View<const T> b, View<T> x, const Launch& L) {
-  const dim3 grid((unsigned)((n + 63) / 64), (unsigned)(L.nact * L.ncps));
-  if (grid.y == 0) return;
+  const unsigned rows = (unsigned)((n + 63) / 64);
+  if (L.nact * L.ncps == 0) return;
   const T* m = reinterpret_cast<const T*>(inv);
   if constexpr (!dense_in_parts<T>(false))
     if (!edge) {
-      k_dense_apply<T><<<grid, 64, 0, L.st>>>(m, (int)n, b, x, L.slots, L.ncps);
+      k_dense_apply<T><<<dim3(rows, (unsigned)(L.nact * L.ncps)), 64, 0, L.st>>>(m, (int)n, b, x, L.slots, L.ncps);
       return;
     }
-  k_dense_apply_parts<T><<<grid, 256, 0, L.st>>>(m, (int)n, b, x, L.slots, L.ncps);
+  // several columns a workgroup where the matrix exceeds an XCD's L2, as long as every compute unit has one
+  auto go = [&](auto ncc) {
+    constexpr int NC = decltype(ncc)::value;
+    const unsigned cols = (unsigned)(L.nact * ((L.ncps + NC - 1) / NC));
+    if (NC > 1 && (2 * n * n * (int64_t)sizeof(T) <= (4 << 20) || rows * cols < 256)) return false;
+    k_dense_apply_parts<T, NC><<<dim3(rows, cols), 64 * kDenseParts, 0, L.st>>>(m, (int)n, b, x, L.slots, L.ncps);
+    return true;
+  };
+  if (!go(std::integral_constant<int, 4>{}) && !go(std::integral_constant<int, 2>{})) go(std::integral_constant<int, 1>{});
 }
 template void dense_apply<double>(const void*, int64_t, bool, View<const double>, View<double>, const Launch&);
 template void dense_apply<float>(const void*, int64_t, bool, View<const float>, View<float>, const Launch&);

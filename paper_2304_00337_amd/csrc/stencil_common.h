@@ -105,39 +105,48 @@ template <>
 __device__ __forceinline__ double fmat<double>(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // Part of row i of x = Inv b for a Hermitian n x n Inv (row i read as the conjugate of column i, so
-// that the lanes of a wave, one row each, read consecutive entries): terms l0 .. l1 - 1, in order,
-// the loads of 16 in flight.  l0 and l1 are the same for the whole wave.  A row is summed in
-// kDenseParts parts [n k / 8, n (k + 1) / 8), which dense_sum combines.
+// that the lanes of a wave, one row each, read consecutive entries), for NC columns of b: terms l0 ..
+// l1 - 1, in order, the loads of 16 in flight.  l0 and l1 are the same for the whole wave.  A row is
+// summed in kDenseParts parts [n k / 8, n (k + 1) / 8), which dense_sum combines.
 constexpr int kDenseParts = 8;
-template <int U, typename T>
-__device__ __forceinline__ void dense_terms(const T* __restrict__ inv, int n, const T* b, int i, int l, int l1, Cx<T>& s) {
+template <int U, int NC, typename T>
+__device__ __forceinline__ void dense_terms(const T* __restrict__ inv, int n, const T* const (&b)[NC], int i, int l, int l1,
+                                            Cx<T> (&s)[NC]) {
   struct alignas(2 * sizeof(T)) Pair {
     T r, i;
   };
   Pair a[U];
-  T br[U], bi[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {   // past the end: zeros times the last entry
     const int k = l + u < l1 ? l + u : l1 - 1;
     a[u] = reinterpret_cast<const Pair*>(inv + 2 * (int64_t)k * n)[i];
-    br[u] = l + u < l1 ? b[k] : (T)0;
-    bi[u] = l + u < l1 ? b[n + k] : (T)0;
   }
 #pragma unroll
-  for (int u = 0; u < U; ++u) {   // s += conj(a) b
-    s.re = fmat<T>(a[u].i, bi[u], fmat<T>(a[u].r, br[u], s.re));
-    s.im = fmat<T>(-a[u].i, br[u], fmat<T>(a[u].r, bi[u], s.im));
+  for (int c = 0; c < NC; ++c) {
+    T br[U], bi[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = l + u < l1 ? l + u : l1 - 1;
+      br[u] = l + u < l1 ? b[c][k] : (T)0;
+      bi[u] = l + u < l1 ? b[c][n + k] : (T)0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {   // s += conj(a) b
+      s[c].re = fmat<T>(a[u].i, bi[u], fmat<T>(a[u].r, br[u], s[c].re));
+      s[c].im = fmat<T>(-a[u].i, br[u], fmat<T>(a[u].r, bi[u], s[c].im));
+    }
   }
 }
-template <typename T>
-__device__ __forceinline__ Cx<T> dense_part(const T* __restrict__ inv, int n, const T* b, int i, int l0, int l1) {
-  Cx<T> s = {0, 0};
+template <int NC, typename T>
+__device__ __forceinline__ void dense_part(const T* __restrict__ inv, int n, const T* const (&b)[NC], int i, int l0, int l1,
+                                           Cx<T> (&s)[NC]) {
+#pragma unroll
+  for (int c = 0; c < NC; ++c) s[c] = Cx<T>{0, 0};
   int l = l0;
 #pragma unroll 1
-  for (; l + 16 <= l1; l += 16) dense_terms<16>(inv, n, b, i, l, l + 16, s);
+  for (; l + 16 <= l1; l += 16) dense_terms<16, NC>(inv, n, b, i, l, l + 16, s);
 #pragma unroll 1
-  for (; l < l1; l += 8) dense_terms<8>(inv, n, b, i, l, l1, s);
-  return s;
+  for (; l < l1; l += 8) dense_terms<8, NC>(inv, n, b, i, l, l1, s);
 }
 // part(k): part k's value of a row
 template <typename F>
