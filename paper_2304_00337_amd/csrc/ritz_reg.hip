@@ -63,7 +63,8 @@ __device__ __forceinline__ double pack_pivot(double d, int i) {
 // one in size, from the signs of the leading minors p_i of T - x I:
 // p_{i+1} = (d_i - x) p_i - e_{i-1}^2 p_{i-1}.  e2 holds the squares, none below 1e-40 (an
 // exact zero minor then passes its neighbour's sign on); a pair of minors shrinks by at most
-// 1e-160 and grows by at most 4^8 in eight rows, after which it is rescaled.
+// 1e-160 in eight rows and, |x| being at most four, grows by at most (1 + 4 + 1)^8, after which it is
+// rescaled.  (A larger x would overflow between two rescalings.)
 __device__ __forceinline__ int sturm_scaled(const double* d, const double* e2, int r, double x) {
   double pm = 1.0, p = d[0] - x;
   int c = p < 0 ? 1 : 0;
@@ -740,7 +741,9 @@ __global__ __launch_bounds__(TY * 16) void k_ritz_reg(const c2* __restrict__ G, 
   // ---- 4. wanted eigenvalues (scaled by 2^-tex during the search) ------------------------------
   const double tiny = 1e-300 + 1e-16 * tn * 1e-10;
   const double lo0 = -1.5, hi0 = 1.5;   // entries and norm are below one
-  const int nz = (zero_thr > -tn - 1.0 && r > 0) ? sturm_scaled(ds, ee2, r, ldexp(zero_thr * (1 + 1e-14) + 1e-300, -tex)) : 0;
+  // (a threshold beyond [lo0, hi0], where no value lies, counts as its end)
+  const double zs = fmin(fmax(ldexp(zero_thr * (1 + 1e-14) + 1e-300, -tex), lo0), hi0);
+  const int nz = (zero_thr > -tn - 1.0 && r > 0) ? sturm_scaled(ds, ee2, r, zs) : 0;
   const int ns = min(want, r - nz);
   {
     // counts at NT points, NT / 64 per octave from 2^-62 to 2^2
