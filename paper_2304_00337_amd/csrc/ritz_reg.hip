@@ -92,9 +92,10 @@ __device__ __forceinline__ int sturm_scaled(const double* d, const double* e2, i
   return c;
 }
 
-// C = op(X) op(Y) as mm_mfma, with the operands of four steps of four loaded ahead, and with
-// UPPER only the output tiles on and above the diagonal (square C).
-template <bool CX, bool TRY, bool UPPER>
+// C = op(X) op(Y) as mm_mfma, with the operands of four steps of four loaded ahead, with UPPER only
+// the output tiles on and above the diagonal (square C), and with HERM (X square) op(X) the Hermitian
+// part of X, which is X itself, bit for bit, where X is Hermitian.
+template <bool CX, bool TRY, bool UPPER, bool HERM = false>
 __device__ __forceinline__ void mm_ahead(const c2* X, int ldx, const c2* Y, int ldy, c2* C, int ldc, int M, int N,
                                          int K, int NB) {
   constexpr int PF = 4;
@@ -112,8 +113,14 @@ __device__ __forceinline__ void mm_ahead(const c2* X, int ldx, const c2* Y, int 
         const bool oa = ia < M && l < K, ob = jb < NB && l < K;
         const c2 a = X[oa ? (CX ? l * ldx + ia : ia * ldx + l) : 0];
         const c2 b = Y[ob ? (TRY ? jb * ldy + l : l * ldy + jb) : 0];
-        ar[u] = oa ? a.r : 0.0;
-        ai[u] = oa ? (CX ? -a.i : a.i) : 0.0;
+        if (HERM) {
+          const c2 t = X[oa ? (CX ? ia * ldx + l : l * ldx + ia) : 0];
+          ar[u] = oa ? 0.5 * (a.r + t.r) : 0.0;
+          ai[u] = oa ? 0.5 * (CX ? t.i - a.i : a.i - t.i) : 0.0;
+        } else {
+          ar[u] = oa ? a.r : 0.0;
+          ai[u] = oa ? (CX ? -a.i : a.i) : 0.0;
+        }
         br[u] = ob ? b.r : 0.0;
         bi[u] = ob ? b.i : 0.0;
       }
@@ -542,7 +549,8 @@ __global__ __launch_bounds__(TY * 16) void k_ritz_reg(const c2* __restrict__ G, 
   if (tid == 0) stamp[2] = (double)wall_clock64();
 
   // ---- 3. H' = Z^* H Z, then its tridiagonal form --------------------------------------------
-  mm_ahead<true, false, false>(H, q, Z, lz, T, lz, q, r, q, r);   // (H is Hermitian)
+  // (of H its Hermitian part, so that one triangle of the second product holds all of H')
+  mm_ahead<true, false, false, true>(H, q, Z, lz, T, lz, q, r, q, r);
   __syncthreads();
   mm_ahead<true, false, true>(Z, lz, T, lz, A, lz, r, r, q, r);
   if (MODE == 1 && WL)   // Z's LDS is reused from the eigenvectors on
