@@ -34,9 +34,12 @@ namespace bl {
 
 namespace {
 
-// size of the per-index arrays (one complex, eight doubles, four ints per basis index) in
-// complex units, rounded up
-__host__ __device__ inline int index_block_c2(int q) { return (q * (16 + 64 + 16) + 15) / 16; }
+// Bytes of dynamic LDS per basis index: one complex, six doubles and two ints, then either the pivot
+// search's two doubles and two ints or, once it is over, a reflector and p (a complex each).
+constexpr size_t kIndexBytes = 16 + 6 * 8 + 2 * 4, kSearchBytes = 2 * 8 + 2 * 4, kReflectorBytes = 2 * 16;
+constexpr int kMaxRitz = 512;
+static_assert(kReflectorBytes >= kSearchBytes, "the reflector's place holds the pivot search");
+static_assert(kMaxRitz * (kIndexBytes + kReflectorBytes) + 256 <= 64 * 1024, "LDS that every launch is granted");
 
 // Number of eigenvalues of the real symmetric tridiagonal (d, e; e[i] couples i, i+1)
 // that are below x (Sturm sequence of the LDL^T factorisation of T - x I).
@@ -60,7 +63,8 @@ __device__ __forceinline__ int sturm_count(const double* d, const double* e2, in
 size_t ritz_small_work_doubles(int q) { return (size_t)10 * q * q + 8 * (size_t)q + 64; }
 
 // Bases wider than the register kernel takes (ritz_reg.hip): four matrices of q rows of stride
-// q | 1 in the work array; LDS holds the index arrays, the current reflector and p.
+// q | 1 in the work array; LDS holds the index arrays, the current reflector and p (53 KB at 512
+// columns, within what any launch may take).
 constexpr int TG = 32;   // TG x TG threads
 __global__ __launch_bounds__(TG * TG) void k_ritz(const c2* __restrict__ G, const c2* __restrict__ H, int q,
                                              int nfix, int want, const double* __restrict__ zthr,
@@ -106,7 +110,7 @@ __global__ __launch_bounds__(TG * TG) void k_ritz(const c2* __restrict__ G, cons
   // that a step needs one barrier (pivot search and update read this step's buffers, the
   // update writes the next step's).  L_{i,k} of the original index i goes to B[i][k]; the
   // rows are put in pivot order afterwards.
-  double* dg = reinterpret_cast<double*>(pinv + q);   // [2][q]
+  double* dg = reinterpret_cast<double*>(reinterpret_cast<char*>(smem) + kIndexBytes * q);   // [2][q]
   int* rem = reinterpret_cast<int*>(dg + 2 * q);      // [2][q]
   for (int i = tid; i < q; i += nt) {
     const double gd = G[i * q + i].r;
@@ -300,7 +304,8 @@ __global__ __launch_bounds__(TG * TG) void k_ritz(const c2* __restrict__ G, cons
   // itself (same lanes, same order: identical values in all waves).
   // the reflector and p are kept in LDS for the products; the reflector also goes to B for the
   // back-transformation
-  c2* vst = smem + index_block_c2(q);
+  // (over the pivot search's arrays)
+  c2* vst = reinterpret_cast<c2*>(dg);
   c2* pv = vst + q;
   for (int k = 0; k + 2 < r; ++k) {
     const int m = r - k - 1;
@@ -661,7 +666,7 @@ void ritz_small(const double* G, const double* H, int q, int nfix, int want, con
   // up to 112 columns the matrix being reduced fits a workgroup's registers (where the device
   // grants its LDS): 0.49 ms there against 1.02 ms here at q = 84, 0.76 against 2.1 at q = 112
   if (ritz_registers(G, H, q, nfix, want, zthr, drop_rel, work, work_stride, Y, theta, count, L)) return;
-  const size_t lds = ((size_t)index_block_c2(q) + 2 * (size_t)q) * sizeof(c2);
+  const size_t lds = (size_t)q * (kIndexBytes + kReflectorBytes);
   k_ritz<<<L.nact, TG * TG, lds, L.st>>>(reinterpret_cast<const c2*>(G), reinterpret_cast<const c2*>(H), q, nfix, want,
                                          zthr, drop_rel, work, work_stride, reinterpret_cast<c2*>(Y), theta, count,
                                          L.slots);
