@@ -61,7 +61,8 @@ typedef struct bl_solver bl_solver;
 
 /* The unit cell and its mesh (Section 3): n x m rectangles of the cell a x b. */
 typedef struct bl_grid {
-  int32_t n, m; /* cells per direction; >= 2, even on every smoothed multigrid level   */
+  int32_t n, m; /* cells per direction; >= 2, even on every smoothed multigrid level,  */
+                /* n * m <= 2^29                                                       */
   double a, b;  /* lattice periods, > 0                                                */
 } bl_grid;
 

@@ -19,6 +19,10 @@
 namespace bl {
 
 constexpr int kMaxLevels = 16;
+// largest grid, n * m cells: the tiled sweeps reach an FP64 plane by 32-bit byte offsets (at 2^29 cells one
+// vector's blocks alone take 400 GB in FP64, 290 GB in mixed precision)
+constexpr int64_t kMaxCells = (int64_t)1 << 29;
+static_assert(kMaxCells * (int64_t)sizeof(double) <= ((int64_t)1 << 32), "byte offsets within a plane");
 constexpr int64_t kMaxCoarse = 2048;   // largest coarsest-level edge count solved densely
 constexpr int64_t kMaxNestedCoarse = 512;   // largest coarsest pencil of the nested start (Ritz kernel)
 constexpr int kMaxSlots = 256;

@@ -138,6 +138,7 @@ int validate_grid(const bl_grid* grid, int p) {
   if (grid->n < 2 || grid->m < 2) return set_error(BL_EINVAL, "n and m must be >= 2%s");
   if (!(grid->a > 0) || !(grid->b > 0) || !std::isfinite(grid->a) || !std::isfinite(grid->b))
     return set_error(BL_EINVAL, "a and b must be positive and finite%s");
+  if ((int64_t)grid->n * grid->m > kMaxCells) return set_error(BL_EINVAL, "n * m must be at most 2^29%s");
   if ((int64_t)p > (int64_t)grid->n * grid->m - 1) return set_error(BL_EINVAL, "nev + nthrow must be <= n*m - 1%s");
   return BL_OK;
 }

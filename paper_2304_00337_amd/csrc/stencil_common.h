@@ -266,8 +266,8 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
   return x * q + (x < r ? x : r) + i;
 }
 
-// The value `off` bytes (below 4 GB) past a base that is uniform in the wave: the base stays in scalar
-// registers and the lane's part of the address is 32 bits.
+// The value `off` bytes past a base that is uniform in the wave: the base stays in scalar registers and
+// the lane's part of the address is 32 bits, which a plane of any grid accepted (kMaxCells) stays below.
 template <typename T>
 __device__ __forceinline__ T& at32(T* base, unsigned off) {
   using C = typename std::conditional<std::is_const<T>::value, const char, char>::type;
