@@ -221,7 +221,6 @@ void zero_cols(View<T> x, int64_t len, const Launch& L);
 constexpr int kMaxFused = 6;
 struct CoarseLevel {
   Geo g;
-  PatchT T4;
   const double* k64;    // kappa, slot-major (nm per slot)
   const float* k32;
   const double* si64;   // patch inverses, slot-major (kPatchW nm per slot); null on the coarsest

@@ -60,14 +60,6 @@ __device__ __forceinline__ double sum4(double a) {
 }
 __device__ __forceinline__ double sum8(double a) { a = sum4(a); return a + dpp_d<kDppHalfMirror>(a); }
 __device__ __forceinline__ double sum16(double a) { a = sum8(a); return a + dpp_d<kDppMirror>(a); }
-// sum over the TG threads of a row of the TG x TG thread grid (16: one row of 16 lanes; 32:
-// two, the second pair of partial sums exchanged across the half-wave)
-template <int TG>
-__device__ __forceinline__ double row_sum(double a) {
-  a = sum16(a);
-  if constexpr (TG == 32) a += __shfl_xor(a, 16, 64);
-  return a;
-}
 
 __device__ __forceinline__ double wave_sum(double a) {
   a = sum16(a);

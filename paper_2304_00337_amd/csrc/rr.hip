@@ -13,10 +13,11 @@
 // other slots of the launch.
 //
 // Bases of at most 96 columns run in one launch on the matrix cores (k_rr_one below).  From there
-// to 144 columns, whose accumulators no workgroup holds, the matrix cores take them in groups: FP64 MFMA 16x16x4 products, the
-// columns cut into groups of 48 (three 16-column tiles): one launch for the diagonal blocks
-// (each group against itself, the upper tile pairs), one for the cross blocks (two groups
-// staged side by side, all nine tile pairs, mirrored into the lower triangle).  One
+// to 144 columns, whose accumulators no workgroup holds, the matrix cores take them in three
+// groups of 48 columns (k_rr_mfma; three 16-column tiles each, FP64 MFMA 16x16x4 products): one
+// launch for the diagonal blocks (each group against itself, the upper tile pairs), one for the
+// cross blocks (two groups staged side by side, all nine tile pairs, mirrored into the lower
+// triangle).  One
 // workgroup of eight waves (four for G, four for H) owns a slice of 16 nodes of a band of
 // rows and one block, and streams the rows through an LDS ring:
 // x-edge rows r-1, r, r+1 and the y-edge row r (with one halo node either side), stored as
@@ -191,7 +192,7 @@ constexpr int SW = 4 * MW;      // nodes per row of a workgroup's slice (one gro
 constexpr int XS = 4;           // x-edge row slots of the ring (rows r-1, r, r+1 in use, r+2 filling)
 constexpr int YW = SW + 2;      // y-edge row with one node either side
 constexpr int RR_THREADS = 128 * MW;
-constexpr int kMfmaGroups = 3;  // bases up to 3 groups (144 columns) take the matrix cores
+constexpr int kMfmaGroups = 3;  // groups of a basis of 97 to 144 columns
 
 // A workgroup stages NG column groups: NG = 1 for a diagonal block of G and H (the upper tile
 // pairs of its three tiles), NG = 2 for the cross block of two groups (all nine tile pairs).
@@ -315,14 +316,14 @@ __device__ __forceinline__ void rr_xrow(int xr, int n, int m, int64_t& off, int&
 // Group bases of workgroup row blockIdx.y: NG = 1, diagonal block y (columns 48 y ..);
 // NG = 2, the y-th cross pair (I < J) in row order.
 template <int NG>
-__device__ __forceinline__ void group_bases(int y, int ngroups, int& cA, int& cB) {
+__device__ __forceinline__ void group_bases(int y, int& cA, int& cB) {
   if (NG == 1) {
     cA = MQ * y;
     cB = cA;
     return;
   }
   int I = 0, rem = y;
-  while (rem >= ngroups - 1 - I) { rem -= ngroups - 1 - I; ++I; }
+  while (rem >= kMfmaGroups - 1 - I) { rem -= kMfmaGroups - 1 - I; ++I; }
   cA = MQ * I;
   cB = MQ * (I + 1 + rem);
 }
@@ -411,7 +412,7 @@ __device__ __forceinline__ void cross_h(const RRStage<2>& st, int s0, int sp, in
 template <int NG>
 __global__ __launch_bounds__(RR_THREADS) void k_rr_mfma(View<const double> Sv, int q, const double* __restrict__ kappa,
                                                         Geo g, const Phase* __restrict__ phs, int slices, int band,
-                                                        int ngroups, double* __restrict__ partial,
+                                                        double* __restrict__ partial,
                                                         const int* __restrict__ slots) {
   using C = RRConf<NG>;
   constexpr int NT = C::NT, MP = C::MP, PT = C::PER_THREAD;
@@ -419,7 +420,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_rr_mfma(View<const double> Sv, i
   RRStage<NG>& st = *reinterpret_cast<RRStage<NG>*>(lds);
   const int slot = slots ? slots[blockIdx.z] : (int)blockIdx.z;
   int cA, cB;
-  group_bases<NG>((int)blockIdx.y, ngroups, cA, cB);
+  group_bases<NG>((int)blockIdx.y, cA, cB);
   const int64_t N = g.ne, nm = g.nm;
   const int n = g.n, m = g.m;
   const double* S = Sv.p + ((int64_t)slot * Sv.cps + Sv.off) * 2 * N;
@@ -1080,10 +1081,10 @@ int rr_gram(View<const double> S, int q, const double* kappa, const Geo& g, cons
     return 0;
   }
   if (q <= kMfmaGroups * MQ) {
+    static_assert(16 * kOneTiles == (kMfmaGroups - 1) * MQ, "every group has columns");
     const RRGrid grd = rr_mfma_grid(g);
     const int nb = grd.blocks;
     if ((int64_t)nb * q * q * 4 * L.nact > partial_cap) return -1;
-    const int ngroups = (q + MQ - 1) / MQ;
     auto launch = [&](auto ngt, int blocks_y) {
       constexpr int NG = decltype(ngt)::value;
       const size_t red = (size_t)2 * 64 * 8 * RRConf<NG>::MP * sizeof(double);
@@ -1094,10 +1095,10 @@ int rr_gram(View<const double> S, int q, const double* kappa, const Geo& g, cons
       }();
       (void)attr;
       k_rr_mfma<NG><<<dim3((unsigned)nb, (unsigned)blocks_y, (unsigned)L.nact), RR_THREADS, lds, L.st>>>(
-          S, q, kappa, g, ph, grd.slices, grd.band, ngroups, partial, L.slots);
+          S, q, kappa, g, ph, grd.slices, grd.band, partial, L.slots);
     };
-    launch(std::integral_constant<int, 1>{}, ngroups);
-    if (ngroups > 1) launch(std::integral_constant<int, 2>{}, ngroups * (ngroups - 1) / 2);
+    launch(std::integral_constant<int, 1>{}, kMfmaGroups);
+    launch(std::integral_constant<int, 2>{}, kMfmaGroups * (kMfmaGroups - 1) / 2);
     const int64_t cnt = (int64_t)q * q * 4;
     k_rr_reduce<<<dim3((unsigned)((cnt + 15) / 16), (unsigned)L.nact), 256, 0, L.st>>>(partial, nb, q, G, H,
                                                                                       L.slots);

@@ -298,7 +298,7 @@ CoarseCycle coarse_cycle(const bl_solver* s, int first, const void* inv, int64_t
   C.ns = s->ns;
   for (int i = 0; i < C.nlev; ++i) {
     const Level& L = s->lv[first + i];
-    C.L[i] = CoarseLevel{L.g, L.T4, L.kappa64, L.kappa32, L.sinv64, L.sinv32};
+    C.L[i] = CoarseLevel{L.g, L.kappa64, L.kappa32, L.sinv64, L.sinv32};
   }
   return C;
 }
