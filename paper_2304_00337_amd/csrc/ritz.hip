@@ -433,10 +433,7 @@ __global__ __launch_bounds__(TG * TG) void k_ritz(const c2* __restrict__ G, cons
   __syncthreads();
   if (tid == 0) stamp[9] = (double)wall_clock64();
   // Eigenvectors: an isolated eigenvalue's from the twisted factorisation (one thread each);
-  // eigenvalues closer than 1e-6 tn form a cluster, whose vectors come from inverse iteration
-  // on T' - lambda I with partial pivoting, one wave per cluster: every lane factorises and
-  // solves for one member, and after each of the three solves the members are Gram-Schmidt-
-  // orthogonalised in order (lanes over the rows, wave reductions).  Real vectors of length r
+  // eigenvalues closer than 1e-6 tn form a cluster (cluster_vectors).  Real vectors of length r
   // are kept in T (as doubles): vec j at xs + j*r.  Per index j the LU of T' - lambda_j I
   // (3 arrays of length r) lies in the free A region, continued in T's tail (at most want*r +
   // 3*want*r <= 4 q^2 doubles, the size of A and T together).
@@ -495,117 +492,8 @@ __global__ __launch_bounds__(TG * TG) void k_ritz(const c2* __restrict__ G, cons
       for (int i = 0; i < r; ++i) x[i] *= inv;
     }
   }
-  {
-    const int wv = tid >> 6, nw = nt >> 6;
-    int ci = 0;
-    for (int j = 0; j < ns;) {
-      int jend = j + 1;
-      while (jend < ns && lam[jend] - lam[jend - 1] <= 1e-6 * tn) ++jend;
-      if (jend - j > 1 && (ci++ % nw) == wv) {
-        const int k = jend - j;
-        for (int c0 = 0; c0 < k; c0 += 64) {   // members, 64 at a time (lanes)
-          const int c = j + c0 + lane;
-          if (c0 + lane < k) {
-            double* u = lu_at(c);
-            double* u1 = u + r;    // U: diagonal and first super-diagonal; the second
-            double* lm = u1 + r;   // super-diagonal is e_{i+1} after a row swap, else 0.
-                                   // Multipliers; a row swap is encoded as -(mult) - 4.
-            const double shift = lam[c];
-            // Gaussian elimination with partial pivoting of the tridiagonal T' - shift I: the
-            // carried row has entries (a_i, b_i) in columns (i, i+1); the next row is
-            // (e_i, d_{i+1} - shift, e_{i+1}) in columns (i, i+1, i+2).
-            // u keeps the reciprocals of U's diagonal (the back substitution multiplies)
-            double a_i = dd[0] - shift, b_i = ee[0];
-            for (int i = 0; i < r - 1; ++i) {
-              const double sub = ee[i];
-              const double dnext = dd[i + 1] - shift, bnext = ee[i + 1];
-              if (fabs(sub) > fabs(a_i)) {              // swap rows i and i+1
-                const double rs = rcp_nr(sub);
-                const double mlt = a_i * rs;
-                u[i] = rs;
-                u1[i] = dnext;
-                lm[i] = -mlt - 4.0;                     // |mult| <= 1, so lm <= -3 marks a swap
-                a_i = b_i - mlt * dnext;
-                b_i = -mlt * bnext;
-              } else {
-                const double aa = fabs(a_i) > tiny ? a_i : (a_i < 0 ? -tiny : tiny);
-                const double ra = rcp_nr(aa);
-                const double mlt = sub * ra;
-                u[i] = ra;
-                u1[i] = b_i;
-                lm[i] = mlt;                            // |mult| <= 1
-                a_i = dnext - mlt * b_i;
-                b_i = bnext;
-              }
-            }
-            u[r - 1] = rcp_nr(fabs(a_i) > tiny ? a_i : (a_i < 0 ? -tiny : tiny));
-            u1[r - 1] = 0.0;
-            lm[r - 1] = 0.0;
-            double* x = xs + (size_t)c * r;
-            for (int i = 0; i < r; ++i) x[i] = 1.0 + 0.0625 * (double)((i * 7 + c * 3) % 11);
-          }
-        }
-        for (int rep = 0; rep < 3; ++rep) {
-          for (int c0 = 0; c0 < k; c0 += 64) {
-            const int c = j + c0 + lane;
-            if (c0 + lane < k) {
-              const double* u = lu_at(c);
-              const double* u1 = u + r;
-              const double* lm = u1 + r;
-              double* x = xs + (size_t)c * r;
-              // forward: apply the row operations to x (the running entry carried in a register)
-              double xi = x[0];
-              for (int i = 0; i < r - 1; ++i) {
-                const double l = lm[i], xn = x[i + 1];
-                if (l <= -3.0) {   // swapped: new row i <- old row i+1; row i+1 <- old i - mult*old i+1
-                  const double mlt = -(l + 4.0);
-                  x[i] = xn;
-                  xi = xi - mlt * xn;
-                } else {
-                  x[i] = xi;
-                  xi = xn - l * xi;
-                }
-              }
-              x[r - 1] = xi;
-              // back substitution with U (reciprocal diagonal u, super u1, super-super e_{i+1}
-              // on swaps; the two entries below carried in registers)
-              double x1 = 0.0, x2 = 0.0;
-              for (int i = r - 1; i >= 0; --i) {
-                double sacc = x[i];
-                if (i + 1 < r) sacc -= u1[i] * x1;
-                if (i + 2 < r && lm[i] <= -3.0) sacc -= ee[i + 1] * x2;
-                const double xv = sacc * u[i];
-                x[i] = xv;
-                x2 = x1;
-                x1 = xv;
-              }
-            }
-          }
-          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-          __builtin_amdgcn_wave_barrier();
-          // orthogonalise each member against the earlier ones, normalise (lanes over rows)
-          for (int c = j; c < jend; ++c) {
-            double* x = xs + (size_t)c * r;
-            for (int pc = j; pc < c; ++pc) {
-              const double* y = xs + (size_t)pc * r;
-              double part = 0;
-              for (int i = lane; i < r; i += 64) part += y[i] * x[i];
-              const double dot = wave_sum(part);
-              for (int i = lane; i < r; i += 64) x[i] -= dot * y[i];
-            }
-            double part = 0;
-            for (int i = lane; i < r; i += 64) part += x[i] * x[i];
-            const double nrm = sqrt(wave_sum(part));
-            const double inv = nrm > 0 ? 1.0 / nrm : 0.0;
-            for (int i = lane; i < r; i += 64) x[i] *= inv;
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-          }
-        }
-      }
-      j = jend;
-    }
-  }
+  cluster_vectors(
+      dd, ee, lam, r, ns, tn, tiny, lu_at, [&](int c) { return xs + (size_t)c * r; }, [](int) {});
   __syncthreads();
   if (tid == 0) stamp[5] = (double)wall_clock64();
 
