@@ -24,6 +24,8 @@
 // From a 32 x 32 level down (FP64): 28 us for edges and 15 us for nodes, against 76 and 41 us
 // with every read wrapped and phased by itself, coefficients loaded per pass and one thread per row of
 // the dense solve.
+// (Not all fits the registers: of the FP64 kernels, nodes with one lane per coarse node spill 17 of them,
+// edges with two lanes one.)
 // A nodal solve of several cycles whose finest level is fused runs them all here, residuals and sums
 // included: two cycles of a 32 x 32 grid take 28 us instead of two launches of 15 with a residual (9) and
 // a sum (5) between.

@@ -552,7 +552,7 @@ void ritz_small(const double* G, const double* H, int q, int nfix, int want, con
                 int* count, const Launch& L) {
   if (L.nact <= 0) return;
   // up to 112 columns the matrix being reduced fits a workgroup's registers (where the device
-  // grants its LDS): 0.49 ms there against 1.02 ms here at q = 84, 0.76 against 2.1 at q = 112
+  // grants its LDS): 0.49 ms there against 1.02 ms here at q = 84, 0.78 against 2.1 at q = 112
   if (ritz_registers(G, H, q, nfix, want, zthr, drop_rel, work, work_stride, Y, theta, count, L)) return;
   const size_t lds = (size_t)q * (kIndexBytes + kReflectorBytes);
   k_ritz<<<L.nact, TG * TG, lds, L.st>>>(reinterpret_cast<const c2*>(G), reinterpret_cast<const c2*>(H), q, nfix, want,

@@ -20,10 +20,11 @@
 //  * eigenvectors: two lanes per vector run the two factorisations of the twisted form at once;
 //  * the back-transformation keeps the vectors in registers and loads the next reflector while
 //    the current one is applied.
-// One call takes 74 / 164 / 258 / 487 / 533 / 757 us at q = 24 / 48 / 64 / 84 / 96 / 112 for q / 2
+// One call takes 77 / 166 / 261 / 488 / 536 / 776 us at q = 24 / 48 / 64 / 84 / 96 / 112 for q / 2
 // values, against 154 / 354 / 608 / 1018 / 1282 / 2140 us with the matrix in LDS or global memory
-// and the steps of ritz.hip.  At q = 84: Cholesky 115 us, H' 65 (half of it the matrix cores' own
-// time on one compute unit), reduction 173, eigenvalues 52, vectors 20, back-transformation 62.
+// and the steps of ritz.hip.  At q = 84: Cholesky 114 us, H' 70 (half of it the matrix cores' own
+// time on one compute unit), reduction 171, eigenvalues 51, vectors 19, back-transformation 62.
+// Beyond 96 columns the registers do not hold everything: 88 of a thread's values go to scratch.
 #include "ritz_ops.h"
 
 #include <type_traits>

@@ -47,8 +47,9 @@ constexpr int kRestrict = 1, kProlong = 2, kBase = 4;
 // the tile's nodes (as the residual kernel computes it), for which the iterate must be exact
 // one node around the tile.
 constexpr int kResid = 8;
-// kZero (nodal forward sweeps): the iterate is zero on entry, not read and not stored before a node's
-// own pass, which leaves out the neighbours that no pass has reached.
+// kZero (forward sweeps): the iterate is zero on entry and not read; nodal sweeps store a node in its own
+// pass first and leave out the neighbours that no pass has reached, edge sweeps take the edges that no
+// pass has written as zero.
 constexpr int kZero = 16;
 constexpr int kLoR = 6;
 constexpr int kHiER = 6;
@@ -195,9 +196,12 @@ struct EdgeArgs {
 // every parity sub-grid) in all passes: its addresses, its seam flags, kappa around it and in FP32 its
 // right-hand side are worked out and loaded once, with the iterate; a sweep from zero neither reads nor
 // stores zeros, and the residual that a restricting sweep forms takes over the iterate's planes, so
-// that the box fits the static LDS in FP64 too.  Loads bound it, two workgroups of 512 threads (105 to
-// 117 registers in FP32) to a compute unit being few to hide them behind: without its arithmetic the
-// sweep takes as long, without the patch inverses a fifth less.  1024 x 1024 FP32, 24 columns, the five
+// that the box fits the static LDS in FP64 too.  Loads bound it, two workgroups of 512 threads to a
+// compute unit (FP32: 92 to 121 registers) or one (FP64: 132 to 160) being few to hide them behind: in
+// FP32, without its arithmetic the sweep takes as long, without the patch inverses a fifth less.  Sweeps
+// without transfers are not the faster form everywhere: 512 x 512 FP32, 24 columns 154 us forward and
+// backward, against 143 and 155 with the patches dealt out; 704 x 640, 48 columns 523 and 520 against
+// 512 and 558.  1024 x 1024 FP32, 24 columns, the five
 // sweep levels of a V-cycle: restricting 778 us, prolongating 949, against 970 and 1028 with the
 // colours' patches dealt out anew in each pass; 256 x 256 FP64, three levels: 134 and 115 us against
 // 182 and 224 with the residual and the transfers in launches of their own.
@@ -293,8 +297,9 @@ __device__ __forceinline__ void edge_tile(T* pl, const T* xc, T* xo, const T* bc
   struct alignas(2 * sizeof(T)) Pair {
     T a, b;
   };
-  // FP32 keeps the block's right-hand side and loads a pass's patch inverse one pass ahead; in FP64
-  // the registers that this takes would halve the waves
+  // FP32 keeps the block's right-hand side and loads a pass's patch inverse one pass ahead (24 columns at
+  // 1024 x 1024: 645 and 617 us, against 679 and 695 without); FP64 loads both in the pass.  There one
+  // workgroup fits a compute unit either way (154 to 160 registers, 162 to 200 with the loads ahead)
   constexpr bool AHEAD = sizeof(T) == 4;
   constexpr int LO = H::LO, BX = H::BX, TX = H::TX;
   constexpr SweepRects R = H::R;
