@@ -116,20 +116,23 @@ __device__ __forceinline__ void dense_terms(const T* __restrict__ inv, int n, co
     T r, i;
   };
   Pair a[U];
+  T br[U], bi[U];
+  auto load_b = [&](int c, int u) {
+    const int k = l + u < l1 ? l + u : l1 - 1;
+    br[u] = l + u < l1 ? b[c][k] : (T)0;
+    bi[u] = l + u < l1 ? b[c][n + k] : (T)0;
+  };
 #pragma unroll
   for (int u = 0; u < U; ++u) {   // past the end: zeros times the last entry
     const int k = l + u < l1 ? l + u : l1 - 1;
     a[u] = reinterpret_cast<const Pair*>(inv + 2 * (int64_t)k * n)[i];
+    if (NC == 1) load_b(0, u);
   }
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    T br[U], bi[U];
+    if (NC > 1)
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int k = l + u < l1 ? l + u : l1 - 1;
-      br[u] = l + u < l1 ? b[c][k] : (T)0;
-      bi[u] = l + u < l1 ? b[c][n + k] : (T)0;
-    }
+      for (int u = 0; u < U; ++u) load_b(c, u);
 #pragma unroll
     for (int u = 0; u < U; ++u) {   // s += conj(a) b
       s[c].re = fmat<T>(a[u].i, bi[u], fmat<T>(a[u].r, br[u], s[c].re));
